@@ -28,7 +28,9 @@ EXTRA = {"gc_mlp.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "gc_push_mlp.hip": 
          # The push kernels of every form must give the same bits: multiply-adds
          # are contracted only within one source expression, never across
          # statements, where the choice would follow each kernel's block layout.
-         "gc_push.hip": ["-ffp-contract=on"]}
+         # No partial redundancy elimination: it would keep the FP64 conversions of
+         # a resident cell's nodes (192 registers) instead of the nodes.
+         "gc_push.hip": ["-ffp-contract=on", "-mllvm", "-enable-pre=false"]}
 
 
 def _compile(src: str) -> str:

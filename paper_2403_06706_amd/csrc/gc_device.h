@@ -15,6 +15,10 @@ constexpr double kC = 299792458.0;                    // speed of light (m/s)
 constexpr double kInvC2 = 1.0 / (299792458.0 * 299792458.0);
 constexpr double kPi = 3.14159265358979323846;
 
+// A condition that seldom holds: its branch is laid out away from the path of
+// the others.
+__device__ __forceinline__ bool rare(bool c) { return __builtin_expect(c, 0); }
+
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror & Shaw, SC'11): ten rounds of the
 // 64x64->128-bit multiply-xor bijection, key advanced by two Weyl constants.
@@ -204,6 +208,175 @@ __device__ __forceinline__ bool gather(const FieldDev &f, R r, R th, R ph, R out
     else return finite12(out);
 }
 
+// ---------------------------------------------------------------------------
+// Cell-resident gathers: a lane keeps the 8 nodes of the cell it evaluated last
+// in registers, as stored, with the cell's origin in index space.  An
+// evaluation in the same cell takes them from there, without the stencil's
+// index arithmetic and without a load: nearly every evaluation at X^{n+1}, which
+// differs from X* of the step before by the corrector's last order, and the
+// X* of a lane that stays in its cell.  The values, their weights and the order
+// of the multiply-adds are those of gather().
+//
+// cell_seek moves to the cell of a point (loading its nodes if it is another
+// one) and leaves the weights of the point; false for a non-finite point.
+// ---------------------------------------------------------------------------
+template <typename R>
+struct CellPos {
+    R fi, fj, zf;        // lower node in index space (zf: phi, not wrapped); NaN: no cell
+    R wr, wt, wp;        // weights of the upper nodes at the point sought last
+    __device__ __forceinline__ CellPos() : fi((R)__builtin_nan("")), fj(fi), zf(fi) {}
+};
+
+// Every weight in [0, 1): as unsigned integers such bit patterns are below that
+// of 1, and those of negative, larger and non-finite values are not.
+__device__ __forceinline__ bool in_unit(double a, double b, double c) {
+    const uint32_t m = max(max((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b)), (uint32_t)__double2hiint(c));
+    return m < 0x3FF00000u;
+}
+__device__ __forceinline__ bool in_unit(float a, float b, float c) {
+    return max(max(__float_as_uint(a), __float_as_uint(b)), __float_as_uint(c)) < 0x3F800000u;
+}
+
+// A value the compiler knows nothing about: a register it need not keep alive
+// before this point.
+template <typename T>
+__device__ __forceinline__ void forget(T &x) { asm volatile("" : "=v"(x)); }
+
+// The nodes of a cell, one lane per particle (FP32 and FP16 fields): chunk c of
+// node h of pair p at q[(2 p + h) 3 + c].
+template <int FDT>
+struct LaneCell {
+    using V = typename std::conditional<FDT == GC_F32, float __attribute__((ext_vector_type(4))),
+                                        uint32_t __attribute__((ext_vector_type(2)))>::type;
+    V q[24];
+    template <typename R>
+    __device__ __forceinline__ void load(const FieldDev &f, const GatherPlan<R> &gp, uint32_t) {
+        constexpr uint32_t E = sizeof(V) / 4;             // bytes of a component
+        const char *b = static_cast<const char *>(f.data);
+#pragma unroll
+        for (int i = 0; i < 24; ++i)
+            q[i] = *reinterpret_cast<const V *>(b + (size_t)((i % 3) * gp.cs) * E + (gp.off[i / 6] + ((i / 3) & 1) * gp.dk) * E);
+    }
+    __device__ __forceinline__ float get(int p, int h, int c, const FieldDev &f) const {
+        const V v = q[(2 * p + h) * 3 + c / 4];
+        if constexpr (FDT == GC_F32) return v[c % 4];
+        else return __half2float(__ushort_as_half((unsigned short)(v[(c % 4) / 2] >> (16 * (c % 2))))) * f.scale[c];
+    }
+    __device__ __forceinline__ void drop() {
+#pragma unroll
+        for (int i = 0; i < 24; ++i) forget(q[i]);
+    }
+    // components [c0, c1) at the weights of at
+    template <int c0, int c1, typename R>
+    __device__ __forceinline__ void value(const FieldDev &f, const CellPos<R> &at, uint32_t, R out[]) const {
+        const R w[4] = {((R)1 - at.wr) * ((R)1 - at.wt), ((R)1 - at.wr) * at.wt, at.wr * ((R)1 - at.wt), at.wr * at.wt};
+#pragma unroll
+        for (int c = c0; c < c1; ++c) out[c] = (R)0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const R wa = w[p] * ((R)1 - at.wp), wb = w[p] * at.wp;
+#pragma unroll
+            for (int c = c0; c < c1; ++c) out[c] = fma(wb, (R)get(p, 1, c, f), fma(wa, (R)get(p, 0, c, f), out[c]));
+        }
+    }
+};
+
+// Word j of lane J of an aligned group of four lanes, to every lane of the
+// group (DPP quad permutation [J, J, J, J]).
+template <int J>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, J * 0x55, 0xF, 0xF, true);
+}
+
+// A value of lane J of an aligned quad, to every lane of the quad.
+template <int J, typename R>
+__device__ __forceinline__ R quad_bcast_value(R x) {
+    static_assert(sizeof(R) % 4 == 0, "whole words");
+    uint32_t w[sizeof(R) / 4];
+    __builtin_memcpy(w, &x, sizeof w);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(R) / 4); ++i) w[i] = quad_bcast<J>(w[i]);
+    R y;
+    __builtin_memcpy(&y, w, sizeof w);
+    return y;
+}
+
+// The nodes of a cell, four lanes of an aligned quad per particle (FP32 and
+// FP64 fields): lane gl keeps components 3gl..3gl+2 (node h of pair p at
+// v[p][3 h + c], from the node records, whose phi pairs are adjacent, 48 or 96
+// bytes each), runs their chains with the operations and order of gather_add,
+// and the quad exchanges the finished components, so all four lanes hold the
+// bits of gather().  Each lane converts and multiplies a quarter of the values.
+// All four lanes must call value together.
+template <int FDT>
+struct QuadCell {
+    using T = typename std::conditional<FDT == GC_F64, double, float>::type;
+    T v[4][6];
+    template <typename R>
+    __device__ __forceinline__ void load(const FieldDev &f, const GatherPlan<R> &gp, uint32_t gl) {
+        const uint32_t row = (uint32_t)(f.nph + 1) * 12u;             // theta stride of the records
+        const uint32_t o[4] = {gp.rec, gp.rec + row, gp.rec + (uint32_t)f.nth * row, gp.rec + (uint32_t)f.nth * row + row};
+        // per-lane 64-bit addresses: the three components of a node merge into one
+        // load and the second node is a constant offset from the first
+        const T *base = static_cast<const T *>(f.rec) + 3u * gl;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const T *p = base + o[q];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                v[q][c] = p[c];            // node k
+                v[q][3 + c] = p[12 + c];   // node k + 1
+            }
+        }
+    }
+    __device__ __forceinline__ void drop() {
+#pragma unroll
+        for (int i = 0; i < 24; ++i) forget(v[i / 6][i % 6]);
+    }
+    template <int c0, int c1, typename R>
+    __device__ __forceinline__ void value(const FieldDev &, const CellPos<R> &at, uint32_t, R out[]) const {
+        const R w[4] = {((R)1 - at.wr) * ((R)1 - at.wt), ((R)1 - at.wr) * at.wt, at.wr * ((R)1 - at.wt), at.wr * at.wt};
+        R acc[3] = {(R)0, (R)0, (R)0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const R wa = w[q] * ((R)1 - at.wp), wb = w[q] * at.wp;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acc[c] = fma(wb, (R)v[q][3 + c], fma(wa, (R)v[q][c], acc[c]));
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if (c0 <= c && c < c1) out[c] = quad_bcast_value<0>(acc[c]);
+            if (c0 <= 3 + c && 3 + c < c1) out[3 + c] = quad_bcast_value<1>(acc[c]);
+            if (c0 <= 6 + c && 6 + c < c1) out[6 + c] = quad_bcast_value<2>(acc[c]);
+            if (c0 <= 9 + c && 9 + c < c1) out[9 + c] = quad_bcast_value<3>(acc[c]);
+        }
+    }
+};
+
+template <int FDT, typename R, typename Cell>
+__device__ __forceinline__ bool cell_seek(const FieldDev &f, R r, R th, R ph, uint32_t gl, CellPos<R> &at, Cell &cell) {
+    const R x = (r - (R)f.r_min) * (R)f.inv_dr;
+    const R y = th * (R)f.inv_dth - (R)0.5;
+    const R z = ph * (R)f.inv_dph;
+    // x - fi is exact when fi = floor(x), unless it rounds to 1, and then, as for
+    // a clamped stencil, the test fails and gather_plan's own weights are taken
+    at.wr = x - at.fi;
+    at.wt = y - at.fj;
+    at.wp = z - at.zf;
+    if (rare(!in_unit(at.wr, at.wt, at.wp))) {
+        GatherPlan<R> gp;
+        if (!gather_plan<FDT>(f, r, th, ph, gp)) return false;
+        at.fi = clampr(floor(x), (R)0, (R)(f.nr - 2));
+        at.fj = clampr(floor(y), (R)0, (R)(f.nth - 2));
+        at.zf = floor(z);
+        at.wr = clampr(x - at.fi, (R)0, (R)1);
+        at.wt = clampr(y - at.fj, (R)0, (R)1);
+        at.wp = z - at.zf;
+        cell.load(f, gp, gl);
+    }
+    return true;
+}
+
 // The field and the extra node array of the full Eqs. 1-2 (same geometry and
 // layout, fx the extra array's description) at one point, with one stencil:
 // the same operations and order as gather() on each array.  Returns what
@@ -234,13 +407,6 @@ __device__ __forceinline__ bool gather2(const FieldDev &f, const FieldDev &fx, R
     return finite12(out);
 }
 
-// Word j of lane J of an aligned group of four lanes, to every lane of the
-// group (DPP quad permutation [J, J, J, J]).
-template <int J>
-__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, J * 0x55, 0xF, 0xF, false);
-}
-
 template <int FDT, int J>
 __device__ __forceinline__ Pair<FDT> quad_bcast_pair(const Pair<FDT> &mine) {
     constexpr int kWords = sizeof(Pair<FDT>) / 4;
@@ -254,73 +420,12 @@ __device__ __forceinline__ Pair<FDT> quad_bcast_pair(const Pair<FDT> &mine) {
     return p;
 }
 
-// A value of lane J of an aligned quad, to every lane of the quad.
-template <int J, typename R>
-__device__ __forceinline__ R quad_bcast_value(R x) {
-    static_assert(sizeof(R) % 4 == 0, "whole words");
-    uint32_t w[sizeof(R) / 4];
-    __builtin_memcpy(w, &x, sizeof w);
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(R) / 4); ++i) w[i] = quad_bcast<J>(w[i]);
-    R y;
-    __builtin_memcpy(&y, w, sizeof w);
-    return y;
-}
-
-// Four lanes of an aligned quad, one particle (FP32 and FP64 fields), on the
-// node records f.rec: lane gl loads components 3gl..3gl+2 of both nodes of the
-// four node pairs (a pair's nodes are adjacent records, 48 or 96 bytes each),
-// runs their chains with the operations and order of gather_add, and the quad
-// exchanges the finished components, so all four lanes hold the bits of
-// gather().  Each lane converts and multiplies a quarter of the values.  All
-// four lanes must call it together.
-template <int FDT, typename R, bool kTame = false>
-__device__ __forceinline__ bool gather_quad_split(const FieldDev &f, R r, R th, R ph, uint32_t gl, R out[12]) {
-    using T = typename std::conditional<FDT == GC_F64, double, float>::type;
-    GatherPlan<R> gp;
-    if (!gather_plan<FDT>(f, r, th, ph, gp)) return false;
-    const uint32_t row = (uint32_t)(f.nph + 1) * 12u;                 // theta stride of the records
-    const uint32_t o[4] = {gp.rec, gp.rec + row, gp.rec + (uint32_t)f.nth * row,
-                           gp.rec + (uint32_t)f.nth * row + row};     // the pairs, in gather_add's order
-    // per-lane 64-bit addresses: the three components of a node merge into one
-    // load and the second node is a constant offset from the first
-    const T *base = static_cast<const T *>(f.rec) + 3u * gl;
-    T v[4][6];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const T *p = base + o[q];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            v[q][c] = p[c];            // node k
-            v[q][3 + c] = p[12 + c];   // node k + 1
-        }
-    }
-    R acc[3] = {(R)0, (R)0, (R)0};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const R wa = gp.w[q] * ((R)1 - gp.wp), wb = gp.w[q] * gp.wp;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[c] = fma(wb, (R)v[q][3 + c], fma(wa, (R)v[q][c], acc[c]));
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        out[c] = quad_bcast_value<0>(acc[c]);
-        out[3 + c] = quad_bcast_value<1>(acc[c]);
-        out[6 + c] = quad_bcast_value<2>(acc[c]);
-        out[9 + c] = quad_bcast_value<3>(acc[c]);
-    }
-    if constexpr (kTame) return true;
-    else return finite12(out);
-}
-
-// Four lanes of an aligned quad, one particle: for FP32 and FP64 fields the
-// component split above; for FP16 fields lane gl loads node pair gl, the quad
-// shares the loaded words, and every lane adds the four pairs in the one-lane
-// order.  Either way all four lanes hold the bits of gather().  All four lanes
+// Four lanes of an aligned quad, one particle, FP16 fields: lane gl loads node
+// pair gl, the quad shares the loaded words, and every lane adds the four pairs
+// in the one-lane order, so all four hold the bits of gather().  All four lanes
 // must call it together.
 template <int FDT, typename R, bool kTame = false>
 __device__ __forceinline__ bool gather_quad(const FieldDev &f, R r, R th, R ph, uint32_t gl, R out[12]) {
-    if constexpr (FDT != GC_F16) return gather_quad_split<FDT, R, kTame>(f, r, th, ph, gl, out);
     GatherPlan<R> gp;
     if (!gather_plan<FDT>(f, r, th, ph, gp)) return false;
     Pair<FDT> mine;
@@ -365,6 +470,14 @@ __device__ __forceinline__ float rsqrt_nr(float x) {
     return y * fmaf(-0.5f * x, y * y, 1.5f);
 }
 
+// A constant held in scalar registers (an FP64 multiply-add takes no literal,
+// and the compiler would keep the series coefficients in vector registers).
+__device__ __forceinline__ double scalar_const(double c) {
+    asm("" : "+s"(c));
+    return c;
+}
+__device__ __forceinline__ float scalar_const(float c) { return c; }
+
 template <typename R>
 __device__ __forceinline__ R sin_0_pi(R x) {
     const R half_pi = (R)1.5707963267948966, pi = (R)3.141592653589793, quarter_pi = (R)0.7853981633974483;
@@ -374,27 +487,27 @@ __device__ __forceinline__ R sin_0_pi(R x) {
     const R z2 = z * z;
     // One series per lane, behind a branch: the particles of a wavefront are
     // binned by cell, so nearly always all of its lanes take the same one.
-    if (use_cos) {
+    if (!rare(!use_cos)) {
         // cos z = 1 - z^2/2! + z^4/4! - ... + z^16/16!
-        R pc = (R)(1.0 / 20922789888000.0);
-        pc = fma(pc, -z2, (R)(1.0 / 87178291200.0));
-        pc = fma(pc, -z2, (R)(1.0 / 479001600.0));
-        pc = fma(pc, -z2, (R)(1.0 / 3628800.0));
-        pc = fma(pc, -z2, (R)(1.0 / 40320.0));
-        pc = fma(pc, -z2, (R)(1.0 / 720.0));
-        pc = fma(pc, -z2, (R)(1.0 / 24.0));
+        R pc = scalar_const((R)(1.0 / 20922789888000.0));
+        pc = fma(pc, -z2, scalar_const((R)(1.0 / 87178291200.0)));
+        pc = fma(pc, -z2, scalar_const((R)(1.0 / 479001600.0)));
+        pc = fma(pc, -z2, scalar_const((R)(1.0 / 3628800.0)));
+        pc = fma(pc, -z2, scalar_const((R)(1.0 / 40320.0)));
+        pc = fma(pc, -z2, scalar_const((R)(1.0 / 720.0)));
+        pc = fma(pc, -z2, scalar_const((R)(1.0 / 24.0)));
         pc = fma(pc, -z2, (R)0.5);
         return fma(pc, -z2, (R)1);
     }
     // sin z = z (1 - z^2/3! + z^4/5! - ... + z^16/17!)
-    R ps = (R)(1.0 / 355687428096000.0);
-    ps = fma(ps, -z2, (R)(1.0 / 1307674368000.0));
-    ps = fma(ps, -z2, (R)(1.0 / 6227020800.0));
-    ps = fma(ps, -z2, (R)(1.0 / 39916800.0));
-    ps = fma(ps, -z2, (R)(1.0 / 362880.0));
-    ps = fma(ps, -z2, (R)(1.0 / 5040.0));
-    ps = fma(ps, -z2, (R)(1.0 / 120.0));
-    ps = fma(ps, -z2, (R)(1.0 / 6.0));
+    R ps = scalar_const((R)(1.0 / 355687428096000.0));
+    ps = fma(ps, -z2, scalar_const((R)(1.0 / 1307674368000.0)));
+    ps = fma(ps, -z2, scalar_const((R)(1.0 / 6227020800.0)));
+    ps = fma(ps, -z2, scalar_const((R)(1.0 / 39916800.0)));
+    ps = fma(ps, -z2, scalar_const((R)(1.0 / 362880.0)));
+    ps = fma(ps, -z2, scalar_const((R)(1.0 / 5040.0)));
+    ps = fma(ps, -z2, scalar_const((R)(1.0 / 120.0)));
+    ps = fma(ps, -z2, scalar_const((R)(1.0 / 6.0)));
     ps = fma(ps, -z2, (R)1);
     return z * ps;
 }
@@ -432,28 +545,26 @@ __device__ __forceinline__ void gc_rhs(R r, R th, R u, R mu, R qm, R iqm, bool d
     const R vEy = (Ez * bx - Ex * bz) * iB;
     const R vEz = (Ex * by - Ey * bx) * iB;
     const R bG = bx * Gx + by * Gy + bz * Gz;
-    R Vx, Vy, Vz, udot;
-    if (drift_free) {
+    const R cG = mu * ig * ig;
+    const R cE = qm * vpar * Epar * ig * (R)kInvC2;
+    const R cK = vpar * vpar;
+    R ax = cG * Gx + cE * vEx + cK * Kx;
+    R ay = cG * Gy + cE * vEy + cK * Ky;
+    R az = cG * Gz + cE * vEz + cK * Kz;
+    if (kFull) {
+        ax += vpar * (x[0] + x[3]) + x[6];
+        ay += vpar * (x[1] + x[4]) + x[7];
+        az += vpar * (x[2] + x[5]) + x[8];
+    }
+    const R pref = gamma * iqm * iB;
+    R Vx = vpar * bx + vEx + pref * (by * az - bz * ay);
+    R Vy = vpar * by + vEy + pref * (bz * ax - bx * az);
+    R Vz = vpar * bz + vEz + pref * (bx * ay - by * ax);
+    R udot = qm * Epar - mu * ig * bG + gamma * vpar * (vEx * Kx + vEy * Ky + vEz * Kz);
+    if (kFull) udot += gamma * (vEx * x[0] + vEy * x[1] + vEz * x[2]);
+    if (rare(drift_free)) {
         Vx = vpar * bx; Vy = vpar * by; Vz = vpar * bz;
         udot = qm * Epar - mu * ig * bG;
-    } else {
-        const R cG = mu * ig * ig;
-        const R cE = qm * vpar * Epar * ig * (R)kInvC2;
-        const R cK = vpar * vpar;
-        R ax = cG * Gx + cE * vEx + cK * Kx;
-        R ay = cG * Gy + cE * vEy + cK * Ky;
-        R az = cG * Gz + cE * vEz + cK * Kz;
-        if (kFull) {
-            ax += vpar * (x[0] + x[3]) + x[6];
-            ay += vpar * (x[1] + x[4]) + x[7];
-            az += vpar * (x[2] + x[5]) + x[8];
-        }
-        const R pref = gamma * iqm * iB;
-        Vx = vpar * bx + vEx + pref * (by * az - bz * ay);
-        Vy = vpar * by + vEy + pref * (bz * ax - bx * az);
-        Vz = vpar * bz + vEz + pref * (bx * ay - by * ax);
-        udot = qm * Epar - mu * ig * bG + gamma * vpar * (vEx * Kx + vEy * Ky + vEz * Kz);
-        if (kFull) udot += gamma * (vEx * x[0] + vEy * x[1] + vEz * x[2]);
     }
     const R ir = rcp_nr(r);
     F[0] = Vx;

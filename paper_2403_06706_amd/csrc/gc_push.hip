@@ -14,7 +14,8 @@
 namespace gc {
 
 // Forms of the push (all bitwise identical in their results):
-//   kFormThroughput  one lane per particle, two node pairs of a gather in registers at a time;
+//   kFormThroughput  one lane per particle, at most 256 registers; a gather that is not
+//                    cell-resident has two node pairs in registers at a time;
 //   kFormAllPairs    one lane per particle, all four pairs of a gather in flight;
 //   kFormQuad        four lanes per particle (an aligned quad): each lane interpolates three
 //                    of the twelve components of every gather (FP16 fields: loads one node
@@ -40,15 +41,15 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
     // The particle of this slot is read from sr at ls and written to st at
     // slot: the same place, or (a reorder's permutation applied by the push)
     // its place in the other state buffer.  In place, a stopped particle costs
-    // one load.  Moved, every field is loaded at once, one round trip after
-    // the permutation's.
+    // one load.  Moved, every field of the step is loaded at once, one round
+    // trip after the permutation's.  What only rare events or the final store
+    // need (id, ensemble index, global index, birth) is read there.
     const SoA &st = a.st, &sr = a.src;
     const bool moved = a.perm != nullptr;
     const uint32_t ls = moved ? a.perm[slot] : slot;
     if (!moved && sr.status[ls] != GC_ACTIVE) return 0;
-    uint32_t status = sr.status[ls], flags = sr.flags[ls], k = sr.k[ls], step = sr.step[ls];
-    const uint32_t ens_raw = sr.ens[ls], pid = sr.id[ls];
-    const uint32_t gid = sr.gid[ls], birth0 = sr.birth[ls];
+    uint32_t status = sr.status[ls], flags = sr.flags[ls], k = sr.k[ls], step0 = sr.step[ls];
+    uint32_t eidx = sr.ens[ls];
     double r0 = sr.r[ls], th0 = sr.th[ls], ph0 = sr.ph[ls], u0 = sr.u[ls], t0 = sr.t[ls];
     double fr0 = sr.fr[ls], fth0 = sr.fth[ls], fph0 = sr.fph[ls], fu0 = sr.fu[ls];
     double mu0 = sr.mu[ls], dtp0 = sr.dtp[ls], s0 = sr.s[ls], ell0 = sr.ell[ls];
@@ -58,7 +59,7 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
     // issued before the status test (else the compiler issues the status load
     // alone, and the others after its round trip).
 #define GC_LOADED(x) asm volatile("" : "+v"(x))
-    GC_LOADED(status); GC_LOADED(flags); GC_LOADED(k); GC_LOADED(step);
+    GC_LOADED(status); GC_LOADED(flags); GC_LOADED(k); GC_LOADED(step0); GC_LOADED(eidx);
     GC_LOADED(r0); GC_LOADED(th0); GC_LOADED(ph0); GC_LOADED(u0); GC_LOADED(t0);
     GC_LOADED(fr0); GC_LOADED(fth0); GC_LOADED(fph0); GC_LOADED(fu0);
     GC_LOADED(mu0); GC_LOADED(dtp0); GC_LOADED(s0); GC_LOADED(ell0);
@@ -66,225 +67,233 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
 #undef GC_LOADED
     // (moved: every slot is active, a reorder puts the active particles first)
     if (status != GC_ACTIVE) return 0;
-    const uint32_t step0 = step;
-    const uint32_t eidx = min(ens_raw, (uint32_t)(kMaxEnsembles - 1));
-    const EnsDev e = a.ens[eidx];
-    uint32_t birth = 0;
-    bool reborn = false;
+    eidx = min(eidx, (uint32_t)(kMaxEnsembles - 1));
+    const EnsDev &e = a.ens[eidx];
     A X0 = (A)r0, X1 = (A)th0, X2 = (A)ph0, X3 = (A)u0;
     A T = (A)t0;
     A c0 = (A)cr0, c1 = (A)cth0, c2 = (A)cph0, c3 = (A)cu0, cT = (A)ct0;
     R fp0 = (R)fr0, fp1 = (R)fth0, fp2 = (R)fph0, fp3 = (R)fu0;
-    R mu = (R)mu0, dtp = (R)dtp0, s = (R)s0, ell = (R)ell0;
+    R mu = (R)mu0, s = (R)s0, ell = (R)ell0;
     const R qm = (R)e.qm, iqm = (R)e.iqm;
     const bool drift_free = e.drift_free != 0;
     const bool scatter = e.lambda > 0.0;
     const R vw = EXT ? (R)e.v_wind : (R)0;          // > 0: scattering centres move with the wind
     const R h = (R)a.dt;
     const double r_in = e.r_in, r_out = e.r_out, th_lo = a.f.th_lo, th_hi = a.f.th_hi;
-
-    for (int it = 0; it < a.n_steps; ++it) {
-        // Field evaluations of the step: at X^n, at X^{n-1} = X^n - dt F^n on
-        // bootstrap steps only, and at the predictor X*.
-        R Fn[4], Fs[4], vpn = 0, vps = 0, tau = 1;
-        // A pending collision k+1 draws its generator block before the first
-        // gather of the step (few live registers here); it is applied once the
-        // gather at X^n gives |B| there.
-        R mun = 0, ell_new = 0;
-        if (flags & GC_FLAG_PENDING) {
-            const CollisionDraw d = draw_collision(pid, k + 1, flags >> GC_FLAG_GEN_SHIFT, e.seed, e.ensemble,
-                                                   e.scatter_law, e.lambda);
-            mun = (R)d.mun;
-            ell_new = (R)d.ell;
+    // Steps to take: the stop step (max_steps, tested after a step) may come first.
+    uint32_t todo = (uint32_t)a.n_steps;
+    uint32_t at_end = GC_ACTIVE;                    // status after todo steps
+    if (e.max_steps > 0) {
+        const int64_t left = max(e.max_steps - (int64_t)step0, (int64_t)1);
+        if (left <= (int64_t)todo) { todo = (uint32_t)left; at_end = GC_FINISHED; }
+    }
+    // Step ratio of the first step; every later one follows a step of size h (or
+    // a bootstrap, whose ratio is 1).
+    R tau = (R)dtp0 == h ? (R)1 : h * rcp_nr((R)dtp0);
+    // The gathers are cell-resident with one lane per particle on FP32 and FP16
+    // fields (96 registers of nodes), and in the quad form on FP32 and FP64 fields
+    // (24 or 48).  The others load every stencil: eight FP64 nodes (192), or the
+    // nodes of both arrays of the full equations, are more than the registers hold.
+    // Bound before: vector issue 0.70 and the gather paths (TA/TD) 0.68/0.73 busy,
+    // both evaluations of a step loading 24 x 16 bytes a lane.  An electron crosses
+    // a cell in about ten steps, so now some lanes of a wavefront load at X*, and
+    // seldom any at X^n.  Per 64-step launch (FP64 on an FP32 256x128x256 field):
+    // 2^20 electrons 2.40 -> 1.91 ms, 1,000 reborn electrons in the quad form
+    // 2.09 -> 1.71 us a step; 300,007 in FP32 arithmetic 0.61 -> 0.39 ms.
+    constexpr bool kResident = !FULL && (FORM == kFormQuad ? FDT != GC_F16 : FDT != GC_F64);
+    using Cell = typename std::conditional<FORM == kFormQuad, QuadCell<FDT == GC_F16 ? GC_F32 : FDT>,
+                                           LaneCell<FDT == GC_F64 ? GC_F32 : FDT>>::type;
+    CellPos<R> at;
+    [[maybe_unused]] Cell cell;
+    constexpr std::integral_constant<int, 0> first;
+    constexpr std::integral_constant<int, 3> three;
+    constexpr std::integral_constant<int, 12> twelve;
+    // move to a point; then its components [c0, c1) into g (xg: the extra node
+    // array); both false where the point cannot be evaluated
+    auto seek = [&](R x, R t, R p) -> bool {
+        if constexpr (kResident) return cell_seek<FDT, R>(a.f, x, t, p, gl, at, cell);
+        else return true;
+    };
+    auto value = [&](auto c0, auto c1, R x, R t, R p, R g[12], R xg[12], bool &xbad) -> bool {
+        xbad = false;
+        if constexpr (kResident) {
+            if constexpr (TAME) cell.template value<c0(), c1(), R>(a.f, at, gl, g);
+            else {
+                cell.template value<0, 12, R>(a.f, at, gl, g);
+                return finite12(g);
+            }
+            return true;
+        } else if constexpr (FULL) {
+            bool xok;
+            const bool ok = gather2<FDT, R, FORM == kFormAllPairs>(a.f, a.fx, x, t, p, g, xg, xok);
+            xbad = !xok;
+            return ok;
         }
+        else if constexpr (FORM == kFormQuad) return gather_quad<FDT, R, TAME>(a.f, x, t, p, gl, g);
+        else return gather<FDT, R, FORM == kFormAllPairs, TAME>(a.f, x, t, p, g);
+    };
+
+    // A bootstrap step needs a third evaluation, F^{n-1} at X^n - dt F^n.  A lane
+    // that bootstraps makes it at the X^n site of the next turn of the loop (its
+    // own step ends one turn later than the others'): in the same turn, every
+    // bootstrap would cost its wavefront an evaluation.  F^n and its speed are
+    // kept in Fb and vpb until then.
+    constexpr uint32_t kBack = GC_FLAG_PENDING << 1;   // internal: this lane is about to evaluate F^{n-1}
+    static_assert(kBack < (1u << GC_FLAG_GEN_SHIFT), "flag bit in use");
+    R Fb[4] = {0, 0, 0, 0}, vpb = 0;
+    uint32_t done = 0;                              // steps taken
+    do {
+        // Rare events (collision, bootstrap, drift-free electrons, exit,
+        // rebirth) stand in branches that the compiler places out of line: a
+        // lone wavefront waits for its instructions after every taken branch.
+        // A point that cannot be evaluated only marks the step as bad; what
+        // follows runs on arbitrary values and is not committed.
+        R Fn[4], Fs[4], vpn, vps;
         R px = (R)X0, pth = (R)X1, pph = (R)X2, pu = (R)X3;
-        bool bad = false;
-        // the gather at a point (xg: the extra node array, full equations only)
-        auto gather_at = [&](R x, R t, R p, R g[12], R xg[12], bool &xok) -> bool {
-            xok = true;
-            if constexpr (FULL) return gather2<FDT, R, FORM == kFormAllPairs>(a.f, a.fx, x, t, p, g, xg, xok);
-            else if constexpr (FORM == kFormQuad) return gather_quad<FDT, R, TAME>(a.f, x, t, p, gl, g);
-            else return gather<FDT, R, FORM == kFormAllPairs, TAME>(a.f, x, t, p, g);
-        };
         auto rhs_at = [&](R x, R t, R u, R g[12], R xg[12], R F[4], R &vp) {
             if constexpr (FULL) gc_rhs<R, true>(x, t, u, mu, qm, iqm, drift_free, g, F, vp, xg);
             else gc_rhs<R>(x, t, u, mu, qm, iqm, drift_free, g, F, vp);
+            if (EXT) vp = path_speed<R>(vp, g, vw);
         };
-        // collision k+1 (Eqs. 9-10) at X^n: |p| kept, new pitch cosine and free path
-        auto collide = [&](const R g[12]) {
-            const R B = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
-            R p2 = pu * pu + (R)2 * mu * B;                  // (p/m)^2, kept in the inertial frame
-            R un;
-            if (EXT && vw > (R)0) wind_collision<R>(pu, mu, B, g[0], vw, mun, un, p2);
-            else un = mun * sqrt(p2);
-            X3 = (A)un;
-            c3 = 0;
-            pu = (R)X3;
-            mu = p2 * ((R)1 - mun * mun) / ((R)2 * B);
-            ell = ell_new;
-            s = 0;
-            k += 1;
-            flags = (flags | GC_FLAG_BOOTSTRAP) & ~GC_FLAG_PENDING;
-            if (a.log_depth > 0 && k <= (uint32_t)a.log_depth && gl == 0)
-                a.log[(size_t)gid * a.log_depth + (k - 1)] = step;
-        };
-        // predictor, Eq. 5
-        auto predict = [&]() {
-            const R wn = (R)1 + (R)0.5 * tau, wq = (R)0.5 * tau;
-            const R d0 = h * (wn * Fn[0] - wq * fp0), d1 = h * (wn * Fn[1] - wq * fp1);
-            const R d2 = h * (wn * Fn[2] - wq * fp2), d3 = h * (wn * Fn[3] - wq * fp3);
-            if (kKahan) {
-                px = (R)(X0 + (d0 - c0)); pth = (R)(X1 + (d1 - c1)); pph = (R)(X2 + (d2 - c2)); pu = (R)(X3 + (d3 - c3));
-            } else {
-                px = (R)(X0 + (A)d0); pth = (R)(X1 + (A)d1); pph = (R)(X2 + (A)d2); pu = (R)(X3 + (A)d3);
-            }
-        };
-        // One gather + right-hand side site that the stages loop through
-        // (stage 0 at X^n, 1 at X^{n-1}, 2 at X*; lanes in different stages run
-        // the same instructions) holds fewer registers than three sites in
-        // straight-line code, which avoid the register copies between stages.
-        // Either gives the same bits (multiply-adds are contracted only within
-        // a source expression).  Three sites where measured faster (the
-        // throughput and quad forms on FP32 fields, reduced equations); the
-        // loop for all pairs of a gather in flight (slower with three sites)
-        // and where three sites spill (full equations, FP64 and FP16 fields).
-        constexpr bool kLoopSites = FORM == kFormAllPairs || FULL || FDT != GC_F32;
-        if constexpr (kLoopSites) {
-            int stage = 0;
-            for (;;) {
-                R g[12], xg[12], F[4], vp;
-                bool xok;
-                if (!gather_at(px, pth, pph, g, xg, xok)) { bad = true; break; }
-                if (stage == 0 && (flags & GC_FLAG_PENDING)) collide(g);
-                if (FULL && !xok) { bad = true; break; }   // after the collision, as the field's own check
-                rhs_at(px, pth, pu, g, xg, F, vp);
-                if (stage == 2) {
-                    Fs[0] = F[0]; Fs[1] = F[1]; Fs[2] = F[2]; Fs[3] = F[3];
-                    vps = EXT ? path_speed<R>(vp, g, vw) : vp;
-                    break;
-                }
-                if (stage == 0) {
-                    Fn[0] = F[0]; Fn[1] = F[1]; Fn[2] = F[2]; Fn[3] = F[3];
-                    vpn = EXT ? path_speed<R>(vp, g, vw) : vp;
-                    if (flags & GC_FLAG_BOOTSTRAP) {
-                        // backward Euler start (Sect. 2.2)
-                        px = (R)X0 - h * F[0]; pth = (R)X1 - h * F[1]; pph = (R)X2 - h * F[2]; pu = (R)X3 - h * F[3];
-                        stage = 1;
-                        continue;
-                    }
-                    tau = dtp == h ? (R)1 : h * rcp_nr(dtp);
-                } else {   // stage 1: F^{n-1} of the bootstrap
-                    fp0 = F[0]; fp1 = F[1]; fp2 = F[2]; fp3 = F[3];
-                    tau = (R)1;
-                    flags &= ~GC_FLAG_BOOTSTRAP;
-                }
-                predict();
-                stage = 2;
-            }
-        } else {
-            // Straight-line sites: no register copies between the stages of a
-            // loop (measured faster for these forms).
-            {   // X^n
-                R g[12], xg[12];
-                bool xok;
-                if (!gather_at(px, pth, pph, g, xg, xok)) {
-                    bad = true;
-                } else {
-                    if (flags & GC_FLAG_PENDING) collide(g);
-                    if (FULL && !xok) {
-                        bad = true;   // after the collision, as the field's own check
-                    } else {
-                        R vp;
-                        rhs_at(px, pth, pu, g, xg, Fn, vp);
-                        vpn = EXT ? path_speed<R>(vp, g, vw) : vp;
-                    }
-                }
-            }
+        if (rare((flags & kBack) != 0)) {
+            // backward Euler start (Sect. 2.2)
+            px = (R)X0 - h * Fb[0]; pth = (R)X1 - h * Fb[1]; pph = (R)X2 - h * Fb[2]; pu = (R)X3 - h * Fb[3];
+        }
+        bool bad = !seek(px, pth, pph);
+        if (rare((flags & GC_FLAG_PENDING) != 0)) {
+            // collision k+1 (Eqs. 9-10) at X^n: |p| kept, new pitch cosine and free path
+            const CollisionDraw d = draw_collision(sr.id[ls], k + 1, flags >> GC_FLAG_GEN_SHIFT, e.seed, e.ensemble,
+                                                   e.scatter_law, e.lambda);
+            R g[12], xg[12];
+            bool xbad;
+            if (!bad) bad = !value(first, three, px, pth, pph, g, xg, xbad);
             if (!bad) {
-                if (flags & GC_FLAG_BOOTSTRAP) {
-                    // backward Euler start (Sect. 2.2): F^{n-1} at X^n - dt F^n
-                    const R bx = (R)X0 - h * Fn[0], bth = (R)X1 - h * Fn[1], bph = (R)X2 - h * Fn[2];
-                    const R bu = (R)X3 - h * Fn[3];
-                    R g[12], xg[12], F[4], vp;
-                    bool xok;
-                    if (!gather_at(bx, bth, bph, g, xg, xok) || (FULL && !xok)) {
-                        bad = true;
+                const R mun = (R)d.mun;
+                const R B = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
+                R p2 = pu * pu + (R)2 * mu * B;                  // (p/m)^2, kept in the inertial frame
+                R un;
+                if (EXT && vw > (R)0) wind_collision<R>(pu, mu, B, g[0], vw, mun, un, p2);
+                else un = mun * sqrt(p2);
+                X3 = (A)un;
+                c3 = 0;
+                pu = (R)X3;
+                mu = p2 * ((R)1 - mun * mun) / ((R)2 * B);
+                ell = (R)d.ell;
+                s = 0;
+                k += 1;
+                flags = (flags | GC_FLAG_BOOTSTRAP) & ~GC_FLAG_PENDING;
+                if (a.log_depth > 0 && k <= (uint32_t)a.log_depth && gl == 0)
+                    a.log[(size_t)sr.gid[ls] * a.log_depth + (k - 1)] = step0 + done;
+            }
+        }
+        {   // X^n (or X^{n-1} of a bootstrap)
+            R g[12], xg[12];
+            bool xbad;
+            bad |= !value(first, twelve, px, pth, pph, g, xg, xbad);
+            if (FULL) bad |= xbad;
+            rhs_at(px, pth, pu, g, xg, Fn, vpn);
+        }
+        bool go = true;
+        if (rare((flags & GC_FLAG_BOOTSTRAP) != 0 && !bad)) {
+            if (!(flags & kBack)) {
+                Fb[0] = Fn[0]; Fb[1] = Fn[1]; Fb[2] = Fn[2]; Fb[3] = Fn[3];
+                vpb = vpn;
+                flags |= kBack;
+                go = false;
+            } else {
+                fp0 = Fn[0]; fp1 = Fn[1]; fp2 = Fn[2]; fp3 = Fn[3];
+                Fn[0] = Fb[0]; Fn[1] = Fb[1]; Fn[2] = Fb[2]; Fn[3] = Fb[3];
+                vpn = vpb;
+                tau = (R)1;
+                flags &= ~(uint32_t)(GC_FLAG_BOOTSTRAP | kBack);
+            }
+        }
+        if (go) {
+            {   // predictor X*, Eq. 5
+                const R wn = (R)1 + (R)0.5 * tau, wq = (R)0.5 * tau;
+                const R d0 = h * (wn * Fn[0] - wq * fp0), d1 = h * (wn * Fn[1] - wq * fp1);
+                const R d2 = h * (wn * Fn[2] - wq * fp2), d3 = h * (wn * Fn[3] - wq * fp3);
+                if (kKahan) {
+                    px = (R)(X0 + (d0 - c0)); pth = (R)(X1 + (d1 - c1)); pph = (R)(X2 + (d2 - c2)); pu = (R)(X3 + (d3 - c3));
+                } else {
+                    px = (R)(X0 + (A)d0); pth = (R)(X1 + (A)d1); pph = (R)(X2 + (A)d2); pu = (R)(X3 + (A)d3);
+                }
+                R g[12], xg[12];
+                bool xbad;
+                bad |= !seek(px, pth, pph);
+                bad |= !value(first, twelve, px, pth, pph, g, xg, xbad);
+                if (FULL) bad |= xbad;
+                rhs_at(px, pth, pu, g, xg, Fs, vps);
+            }
+            if (rare(bad)) {
+                status = GC_NONFINITE;
+                todo = 0;
+            } else {
+                // corrector, Eq. 6: dt/(6(1+tau)) [(1+tau)(3+tau) F^n + (3+2 tau) F* - tau^2 F^{n-1}]
+                R cf = h * (R)(1.0 / 12.0);
+                if (rare(tau != (R)1)) cf = h * rcp_nr((R)6 * ((R)1 + tau));
+                const R an = ((R)1 + tau) * ((R)3 + tau), as = (R)3 + (R)2 * tau, ap = tau * tau;
+                const R e0 = cf * (an * Fn[0] + as * Fs[0] - ap * fp0);
+                const R e1 = cf * (an * Fn[1] + as * Fs[1] - ap * fp1);
+                const R e2 = cf * (an * Fn[2] + as * Fs[2] - ap * fp2);
+                const R e3 = cf * (an * Fn[3] + as * Fs[3] - ap * fp3);
+                tau = (R)1;
+                // path along the field line over the step (trapezoid of |v_par|), Eq. 9
+                const R s1 = s + (R)0.5 * (fabs(vpn) + fabs(vps)) * h;
+                s = scatter ? s1 : s;
+                flags |= scatter && s >= ell ? (uint32_t)GC_FLAG_PENDING : 0u;
+                if (kKahan) {
+                    kahan_add(X0, c0, (A)e0); kahan_add(X1, c1, (A)e1);
+                    kahan_add(X2, c2, (A)e2); kahan_add(X3, c3, (A)e3);
+                    kahan_add(T, cT, (A)h);
+                } else {
+                    X0 += (A)e0; X1 += (A)e1; X2 += (A)e2; X3 += (A)e3;
+                    T += (A)a.dt;
+                }
+                fp0 = Fn[0]; fp1 = Fn[1]; fp2 = Fn[2]; fp3 = Fn[3];
+                done += 1;
+                const double r = (double)X0, th = (double)X1;
+                const bool inside = r >= r_in && r <= r_out && th >= th_lo && th <= th_hi;   // false for non-finite r, th
+                if (rare(!(inside && isfinite(X2) && isfinite(X3)))) {
+                    if (!(isfinite(X0) && isfinite(X1) && isfinite(X2) && isfinite(X3))) {
+                        status = GC_NONFINITE;
+                        todo = 0;
+                    } else if (!EXT || (int64_t)(step0 + done) >= e.rebirth_steps) {
+                        status = GC_EXITED;
+                        todo = 0;
                     } else {
-                        rhs_at(bx, bth, bu, g, xg, F, vp);
-                        fp0 = F[0]; fp1 = F[1]; fp2 = F[2]; fp3 = F[3];
-                        tau = (R)1;
-                        flags &= ~GC_FLAG_BOOTSTRAP;
+                        // rebirth (continuous injection, Sect. 3): the next generation starts
+                        // from the injection state with its own generator stream
+                        const uint32_t gen = (flags >> GC_FLAG_GEN_SHIFT) + 1;
+                        const BirthState b = rebirth_state<FDT>(a.fdev, a.ens + eidx, sr.id[ls], gen);
+                        if constexpr (kResident) {   // another cell: its nodes need not be kept over the call
+                            at = CellPos<R>();
+                            cell.drop();
+                        }
+                        X0 = (A)b.r; X1 = (A)b.th; X2 = (A)b.ph; X3 = (A)b.u;
+                        c0 = 0; c1 = 0; c2 = 0; c3 = 0; cT = 0; T = 0;
+                        fp0 = 0; fp1 = 0; fp2 = 0; fp3 = 0;
+                        mu = (R)b.mu; s = 0; ell = (R)b.ell;
+                        k = 0;
+                        flags = GC_FLAG_BOOTSTRAP | (gen << GC_FLAG_GEN_SHIFT);
+                        if (gl == 0) {
+                            st.birth[slot] = step0 + done;
+                            if (a.log_depth > 0) {
+                                uint32_t *row = a.log + (size_t)sr.gid[ls] * a.log_depth;
+                                for (int j = 0; j < a.log_depth; ++j) row[j] = 0xFFFFFFFFu;
+                            }
+                        }
+                        if (b.status != GC_ACTIVE) {
+                            status = b.status;
+                            todo = 0;
+                        }
                     }
-                } else {
-                    tau = dtp == h ? (R)1 : h * rcp_nr(dtp);
-                }
-            }
-            if (!bad) {   // X*
-                predict();
-                R g[12], xg[12], vp;
-                bool xok;
-                if (!gather_at(px, pth, pph, g, xg, xok) || (FULL && !xok)) {
-                    bad = true;
-                } else {
-                    rhs_at(px, pth, pu, g, xg, Fs, vp);
-                    vps = EXT ? path_speed<R>(vp, g, vw) : vp;
                 }
             }
         }
-        if (bad) { status = GC_NONFINITE; break; }
-        // corrector, Eq. 6: dt/(6(1+tau)) [(1+tau)(3+tau) F^n + (3+2 tau) F* - tau^2 F^{n-1}]
-        const R cf = tau == (R)1 ? h * (R)(1.0 / 12.0) : h * rcp_nr((R)6 * ((R)1 + tau));
-        const R an = ((R)1 + tau) * ((R)3 + tau), as = (R)3 + (R)2 * tau, ap = tau * tau;
-        const R e0 = cf * (an * Fn[0] + as * Fs[0] - ap * fp0);
-        const R e1 = cf * (an * Fn[1] + as * Fs[1] - ap * fp1);
-        const R e2 = cf * (an * Fn[2] + as * Fs[2] - ap * fp2);
-        const R e3 = cf * (an * Fn[3] + as * Fs[3] - ap * fp3);
-        // path along the field line over the step (trapezoid of |v_par|), Eq. 9
-        if (scatter) {
-            s += (R)0.5 * (fabs(vpn) + fabs(vps)) * h;
-            if (s >= ell) flags |= GC_FLAG_PENDING;
-        }
-        A n0, n1, n2, n3;
-        A nc0 = c0, nc1 = c1, nc2 = c2, nc3 = c3;   // new compensation terms (Kahan form)
-        if (kKahan) {
-            n0 = X0; n1 = X1; n2 = X2; n3 = X3;
-            kahan_add(n0, nc0, (A)e0); kahan_add(n1, nc1, (A)e1);
-            kahan_add(n2, nc2, (A)e2); kahan_add(n3, nc3, (A)e3);
-        } else {
-            n0 = X0 + (A)e0; n1 = X1 + (A)e1; n2 = X2 + (A)e2; n3 = X3 + (A)e3;
-        }
-        X0 = n0; X1 = n1; X2 = n2; X3 = n3;
-        c0 = nc0; c1 = nc1; c2 = nc2; c3 = nc3;
-        fp0 = Fn[0]; fp1 = Fn[1]; fp2 = Fn[2]; fp3 = Fn[3];
-        dtp = h;
-        if (kKahan) kahan_add(T, cT, (A)h);
-        else T += (A)a.dt;
-        step += 1;
-        if (!(isfinite(n0) && isfinite(n1) && isfinite(n2) && isfinite(n3))) { status = GC_NONFINITE; break; }
-        const double r = (double)X0, th = (double)X1;
-        if (r < r_in || r > r_out || th < th_lo || th > th_hi) {
-            if (!EXT || (int64_t)step >= e.rebirth_steps) { status = GC_EXITED; break; }
-            // rebirth (continuous injection, Sect. 3): the next generation starts
-            // from the injection state with its own generator stream
-            const uint32_t gen = (flags >> GC_FLAG_GEN_SHIFT) + 1;
-            const BirthState b = rebirth_state<FDT>(a.fdev, a.ens + eidx, pid, gen);
-            X0 = (A)b.r; X1 = (A)b.th; X2 = (A)b.ph; X3 = (A)b.u;
-            c0 = 0; c1 = 0; c2 = 0; c3 = 0; cT = 0; T = 0;
-            fp0 = 0; fp1 = 0; fp2 = 0; fp3 = 0;
-            mu = (R)b.mu; dtp = 0; s = 0; ell = (R)b.ell;
-            k = 0;
-            flags = GC_FLAG_BOOTSTRAP | (gen << GC_FLAG_GEN_SHIFT);
-            birth = step;
-            reborn = true;
-            if (a.log_depth > 0 && gl == 0) {
-                uint32_t *row = a.log + (size_t)gid * a.log_depth;
-                for (int j = 0; j < a.log_depth; ++j) row[j] = 0xFFFFFFFFu;
-            }
-            if (b.status != GC_ACTIVE) { status = b.status; break; }
-        }
-        if (e.max_steps > 0 && (int64_t)step >= e.max_steps) { status = GC_FINISHED; break; }
-    }
+    } while (done < todo);
     if (gl != 0) return 0;
+    if (status == GC_ACTIVE) status = at_end;
     st.r[slot] = (double)X0; st.th[slot] = (double)X1; st.ph[slot] = (double)X2; st.u[slot] = (double)X3;
     if (kKahan) {
         st.cr[slot] = (double)c0; st.cth[slot] = (double)c1; st.cph[slot] = (double)c2;
@@ -292,12 +301,19 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
     }
     st.t[slot] = (double)T;
     st.fr[slot] = (double)fp0; st.fth[slot] = (double)fp1; st.fph[slot] = (double)fp2; st.fu[slot] = (double)fp3;
-    st.mu[slot] = (double)mu; st.dtp[slot] = (double)dtp; st.s[slot] = (double)s; st.ell[slot] = (double)ell;
-    st.k[slot] = k; st.flags[slot] = flags; st.status[slot] = status; st.step[slot] = step;
-    // (in place these rewrite the values loaded: no branch, and no flag kept over the loop)
-    st.id[slot] = pid; st.ens[slot] = ens_raw; st.gid[slot] = gid;
-    st.birth[slot] = reborn ? birth : birth0;
-    return step - step0;
+    st.mu[slot] = (double)mu; st.s[slot] = (double)s; st.ell[slot] = (double)ell;
+    // step size of the last step; 0 for a generation that has not taken one
+    const uint32_t flags0 = sr.flags[ls];
+    const bool reborn = EXT && (flags >> GC_FLAG_GEN_SHIFT) != (flags0 >> GC_FLAG_GEN_SHIFT);
+    const bool fresh = reborn && st.birth[slot] == step0 + done;
+    st.dtp[slot] = fresh ? 0.0 : done > 0 ? (double)h : (double)(R)sr.dtp[ls];
+    st.k[slot] = k; st.status[slot] = status; st.step[slot] = step0 + done;
+    if (moved) {
+        st.id[slot] = sr.id[ls]; st.ens[slot] = sr.ens[ls]; st.gid[slot] = sr.gid[ls];
+        if (!reborn) st.birth[slot] = sr.birth[ls];
+    }
+    st.flags[slot] = flags & ~kBack;
+    return done;
 }
 
 // Grid form: one slot per G lanes.  Workgroups are dispatched round-robin over

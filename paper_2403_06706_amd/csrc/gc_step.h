@@ -24,12 +24,14 @@ __device__ __forceinline__ void kahan_add(A &x, A &c, A d) {
 
 // Generator block of collision k1 of generation gen (counter (id, k1, 0, gen),
 // key (seed, ensemble)): new pitch cosine from a1 (Eq. 10, or Eq. 12 with the
-// sign from a2) and the next free path -lambda ln(1 - a0).  Kept out of line:
-// it runs for a few steps in a thousand, and inlined it would raise the push's
-// register count.
+// sign from a2) and the next free path -lambda ln(1 - a0).  The grid push has it
+// inline, where no gathered value is live: a call would keep its resident cell
+// in the registers that a callee saves.  The network push calls it
+// (draw_collision_call): it runs for a few steps in a thousand, and inlined it
+// would raise that kernel's register count.
 struct CollisionDraw { double mun, ell; };
 
-__device__ __noinline__ CollisionDraw draw_collision(uint32_t pid, uint32_t k1, uint32_t gen, uint64_t seed,
+__device__ __forceinline__ CollisionDraw draw_collision(uint32_t pid, uint32_t k1, uint32_t gen, uint64_t seed,
                                                      uint32_t ens, int law, double lambda) {
     const U64x4 rb = philox4x64_10(pid, k1, kPurposePath, gen, seed, ens);
     const double a0 = u01(rb.v[0]), a1 = u01(rb.v[1]), a2 = u01(rb.v[2]);
@@ -37,6 +39,10 @@ __device__ __noinline__ CollisionDraw draw_collision(uint32_t pid, uint32_t k1, 
     d.mun = law == 1 ? (a2 < 0.5 ? -1.0 : 1.0) * sqrt(a1) : 1.0 - 2.0 * a1;
     d.ell = -lambda * log(1.0 - a0);
     return d;
+}
+__device__ __noinline__ CollisionDraw draw_collision_call(uint32_t pid, uint32_t k1, uint32_t gen, uint64_t seed,
+                                                          uint32_t ens, int law, double lambda) {
+    return draw_collision(pid, k1, gen, seed, ens, law, lambda);
 }
 
 // Collision in the frame of the scattering centres when they move with a
