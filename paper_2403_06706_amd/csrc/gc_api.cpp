@@ -98,6 +98,7 @@ struct gc_ctx {
     int tail_skip = 0;                         // reorders still to skip in the tail
     hipEvent_t ahead[4] = {nullptr, nullptr, nullptr, nullptr};   // ends of the last chunks issued
     int ahead_pos = 0;
+    uint32_t since_change = 0;                 // keep_close calls since the particle set changed
     // timing
     struct PushEv { hipEvent_t e0, e1; int form; };
     std::vector<PushEv> ev_push;
@@ -302,32 +303,48 @@ uint32_t bits_for(uint32_t max_key) {
 // Tail of a run (eager advance only): once the live count read back from an
 // earlier reorder is below tail_threshold, the machine is far from full and the
 // push is bound by each wavefront's chain of dependent memory round trips.
-// Then the push takes a latency form (all loads of a gather in flight; below
-// threshold / kQuadShare, four lanes per particle), and the reorder runs
-// only every kTailReorderEvery chunks (particles cross about two cells per 64
-// steps, so the cell order decays slowly, while a reorder costs a fixed ~80 us
-// of launches).  No choice changes any particle's trajectory.
-constexpr int kTailReorderEvery = 8;
+// Then the push takes a latency form (below quad_limit four lanes per
+// particle; the full equations all loads of a gather in flight), and the
+// reorder runs only every kTailReorderEvery chunks (particles cross about two
+// cells per 64 steps, so the cell order decays slowly, while a reorder costs a
+// fixed ~70 us of launches).  The full equations load two whole stencils per
+// evaluation and feel the decay more: every 4 chunks (90,001 electrons, 1,024
+// steps: 13.0 ms every 8, 12.4 every 4, 11.9 every 2; 5,000: 6.30, 6.26, 6.31).
+// No choice changes any particle's trajectory.
+constexpr int kTailReorderEvery = 8, kTailReorderEveryFull = 4;
 // The live count read back is only as fresh as the host's lead over the
 // device: with the tail policy on, the host issues a chunk only once the chunk
 // issued kAhead chunks earlier has finished (enough queued work to hide the
 // launches, little enough for the count to follow the run).
 constexpr int kAhead = 3;
 
+// The live count as far as the host knows it: read back from an earlier
+// reorder, 0xFFFFFFFF if none was since the particle set changed.
 uint32_t seen_count(const gc_ctx *ctx) {
     if (ctx->opt.tail_threshold <= 0 || ctx->capturing || !ctx->count_host) return 0xFFFFFFFFu;
     return *ctx->count_host;
 }
 
+// An upper bound of it for the eager chunks: at most every particle is live, so
+// a small set takes the tail's forms from its first chunk (the first chunks of
+// 1,024 electrons took the throughput form: 0.19 ms each against 0.09).
+uint32_t live_bound(const gc_ctx *ctx) {
+    if (ctx->opt.tail_threshold <= 0 || ctx->capturing) return 0xFFFFFFFFu;
+    return (uint32_t)std::min<uint64_t>(seen_count(ctx), ctx->n);
+}
+
+// Reorders are skipped only once a count has been read back, and not before the
+// host is sure to have one (keep_close): on a count that happens to arrive
+// earlier the schedule of reorders would depend on timing.
 bool tail_mode(const gc_ctx *ctx) {
-    const uint32_t seen = seen_count(ctx);
-    return seen != 0xFFFFFFFFu && seen < (uint32_t)ctx->opt.tail_threshold;
+    return ctx->since_change > (uint32_t)kAhead && seen_count(ctx) < (uint32_t)ctx->opt.tail_threshold;
 }
 
 int push_form(const gc_ctx *ctx) {
-    const uint32_t seen = seen_count(ctx);
-    if (seen == 0xFFFFFFFFu || seen >= (uint32_t)ctx->opt.tail_threshold) return 0;
-    return seen < (uint32_t)ctx->opt.tail_threshold / kQuadShare ? 2 : 1;
+    const uint32_t n = live_bound(ctx), T = (uint32_t)ctx->opt.tail_threshold;
+    if (n >= T) return 0;
+    const bool f64 = ctx->opt.precision == GC_PREC_F64, full = ctx->fx.data != nullptr;
+    return n < quad_limit(T, f64, ctx->f.dtype, full, false) ? 2 : 1;
 }
 
 gc_status finish_reorder(gc_ctx *ctx, int order, hipEvent_t e0, hipEvent_t e1, hipEvent_t p0, hipEvent_t p1);
@@ -421,8 +438,7 @@ gc_status push(gc_ctx *ctx, double dt, int32_t steps, bool timed) {
     a.n_slots = (uint32_t)ctx->n;
     a.n_steps = steps;
     a.dt = dt;
-    int form = ctx->opt.field_source == GC_SOURCE_MLP || ctx->opt.persistent ? 0 : push_form(ctx);
-    if (form == 2 && ctx->fx.data) form = 1;      // the full equations have no quad form
+    const int form = ctx->opt.field_source == GC_SOURCE_MLP || ctx->opt.persistent ? 0 : push_form(ctx);
     a.steps_done = ctx->steps + form;
     a.log = ctx->log;
     a.log_depth = ctx->opt.log_depth;
@@ -468,6 +484,7 @@ gc_status keep_close(gc_ctx *ctx) {
     else HIPCHK(hipEventSynchronize(ev));
     HIPCHK(hipEventRecord(ev, ctx->stream));
     ctx->ahead_pos = (ctx->ahead_pos + 1) % kAhead;
+    if (ctx->since_change <= (uint32_t)kAhead) ++ctx->since_change;
     return GC_OK;
 }
 
@@ -479,7 +496,7 @@ gc_status enqueue_advance(gc_ctx *ctx, double dt, int64_t n_steps, bool timed) {
         gc_status st = GC_OK;
         if (!tail || ctx->bound_dirty || ctx->tail_skip <= 0) {
             st = reorder(ctx, timed && ctx->opt.timing == 1, ctx->opt.order);   // (timing 2: pushes only)
-            ctx->tail_skip = kTailReorderEvery - 1;
+            ctx->tail_skip = (ctx->fx.data ? kTailReorderEveryFull : kTailReorderEvery) - 1;
         } else {
             --ctx->tail_skip;
         }
@@ -843,6 +860,7 @@ gc_status gc_inject(gc_ctx *ctx, const gc_inject_desc *d) {
     ctx->bound_dirty = true;
     ctx->order_known = ctx->keys_known = false;
     if (ctx->count_host) *ctx->count_host = 0xFFFFFFFFu;
+    ctx->since_change = 0;
     return GC_OK;
 }
 
@@ -863,7 +881,8 @@ gc_status gc_advance_graph(gc_ctx *ctx, double dt, int64_t n_steps) {
     // The tail: once the live count read back is below tail_threshold, a replay
     // would mostly pay for its fixed launches (a reorder every chunk); the chunks
     // then run eagerly with the tail policy (bitwise the same results).
-    if (tail_mode(ctx) && ctx->opt.order != GC_ORDER_NONE) return enqueue_advance(ctx, dt, n_steps, ctx->opt.timing != 0);
+    if (seen_count(ctx) < (uint32_t)ctx->opt.tail_threshold && ctx->opt.order != GC_ORDER_NONE)
+        return enqueue_advance(ctx, dt, n_steps, ctx->opt.timing != 0);
     // reset the live prefix now, never inside a graph: captured, the reset would
     // make every replay sort and copy the stopped particles again
     if (ctx->bound_dirty && ctx->opt.order != GC_ORDER_NONE) {
@@ -997,6 +1016,7 @@ gc_status gc_set_state(gc_ctx *ctx, const gc_state_view *src, uint64_t n) {
     ctx->bound_dirty = true;
     ctx->order_known = ctx->keys_known = false;
     if (ctx->count_host) *ctx->count_host = 0xFFFFFFFFu;
+    ctx->since_change = 0;
     if (ctx->gexec) {
         (void)hipGraphExecDestroy(ctx->gexec);
         ctx->gexec = nullptr;

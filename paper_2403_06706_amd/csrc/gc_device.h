@@ -407,39 +407,6 @@ __device__ __forceinline__ bool gather2(const FieldDev &f, const FieldDev &fx, R
     return finite12(out);
 }
 
-template <int FDT, int J>
-__device__ __forceinline__ Pair<FDT> quad_bcast_pair(const Pair<FDT> &mine) {
-    constexpr int kWords = sizeof(Pair<FDT>) / 4;
-    static_assert(sizeof(Pair<FDT>) % 4 == 0, "pair storage must be whole words");
-    uint32_t w[kWords];
-    __builtin_memcpy(w, &mine, sizeof w);
-#pragma unroll
-    for (int i = 0; i < kWords; ++i) w[i] = quad_bcast<J>(w[i]);
-    Pair<FDT> p;
-    __builtin_memcpy(&p, w, sizeof w);
-    return p;
-}
-
-// Four lanes of an aligned quad, one particle, FP16 fields: lane gl loads node
-// pair gl, the quad shares the loaded words, and every lane adds the four pairs
-// in the one-lane order, so all four hold the bits of gather().  All four lanes
-// must call it together.
-template <int FDT, typename R, bool kTame = false>
-__device__ __forceinline__ bool gather_quad(const FieldDev &f, R r, R th, R ph, uint32_t gl, R out[12]) {
-    GatherPlan<R> gp;
-    if (!gather_plan<FDT>(f, r, th, ph, gp)) return false;
-    Pair<FDT> mine;
-    mine.load(f.data, gp.off[gl], gp.dk, gp.cs);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) out[c] = (R)0;
-    gather_add<FDT, R>(f, gp, 0, quad_bcast_pair<FDT, 0>(mine), out);
-    gather_add<FDT, R>(f, gp, 1, quad_bcast_pair<FDT, 1>(mine), out);
-    gather_add<FDT, R>(f, gp, 2, quad_bcast_pair<FDT, 2>(mine), out);
-    gather_add<FDT, R>(f, gp, 3, quad_bcast_pair<FDT, 3>(mine), out);
-    if constexpr (kTame) return true;
-    else return finite12(out);
-}
-
 // ---------------------------------------------------------------------------
 // Reciprocal, inverse square root and sine for the right-hand side.
 // Hardware estimates refined by Newton steps (two in double, one in float:
@@ -525,9 +492,11 @@ __device__ __forceinline__ R sin_0_pi(R x) {
 // point: v_par (x0..2 + x3..5) + x6..8 joins the bracket of dR/dt and
 // gamma v_E.x0..2 joins du/dt.
 // ---------------------------------------------------------------------------
+// ir, is: 1/r and 1/sin(th), which the caller may compute while the field at the
+// point is still on its way.
 template <typename R, bool kFull = false>
-__device__ __forceinline__ void gc_rhs(R r, R th, R u, R mu, R qm, R iqm, bool drift_free,
-                                       const R g[12], R F[4], R &vpar, const R *x = nullptr) {
+__device__ __forceinline__ void gc_rhs_at(R ir, R is, R u, R mu, R qm, R iqm, bool drift_free,
+                                          const R g[12], R F[4], R &vpar, const R *x = nullptr) {
     const R Bx = g[0], By = g[1], Bz = g[2];
     const R Ex = g[3], Ey = g[4], Ez = g[5];
     const R Gx = g[6], Gy = g[7], Gz = g[8];
@@ -566,11 +535,15 @@ __device__ __forceinline__ void gc_rhs(R r, R th, R u, R mu, R qm, R iqm, bool d
         Vx = vpar * bx; Vy = vpar * by; Vz = vpar * bz;
         udot = qm * Epar - mu * ig * bG;
     }
-    const R ir = rcp_nr(r);
     F[0] = Vx;
     F[1] = Vy * ir;
-    F[2] = Vz * ir * rcp_nr(sin_0_pi(th));
+    F[2] = Vz * ir * is;
     F[3] = udot;
+}
+template <typename R>
+__device__ __forceinline__ void gc_rhs(R r, R th, R u, R mu, R qm, R iqm, bool drift_free, const R g[12], R F[4],
+                                       R &vpar) {
+    gc_rhs_at<R>(rcp_nr(r), rcp_nr(sin_0_pi(th)), u, mu, qm, iqm, drift_free, g, F, vpar);
 }
 
 }  // namespace gc

@@ -8,9 +8,28 @@
 namespace gc {
 
 constexpr int kMaxEnsembles = 4096;
-// Tail policy: below tail_threshold / kQuadShare live particles the push takes
-// the four-lanes-per-particle form (above it, in the tail, all pairs in flight).
-constexpr uint32_t kQuadShare = 4;
+// Tail policy: fewer live particles than this (a share of the tail threshold T)
+// take the four-lanes-per-particle form; from there to T, one lane per particle.
+// The line lies where the quad form's wavefronts begin to share a SIMD (1,024 of
+// 16 particles, T/8 of the default 131,072), measured per 1,024 steps:
+//  * FP64 arithmetic on FP32 fields: 12,000 particles 2.26 ms (quad) against 2.82
+//    (lane), 20,011 3.03 against 2.90;
+//  * FP32 arithmetic on FP32 fields, whose shorter step gains from two quad
+//    wavefronts per SIMD: T/4 (30,000: 2.33 against 2.41; 50,000 the lane form);
+//  * FP64 fields: T, because the lane form cannot keep a cell of them and feels
+//    the order decay between the tail's rare reorders (50,000: 4.7 against 8.9 ms,
+//    128,000: 9.1 against 18.8; 250,000: 8.5 against 8.2 per 512).  Reordered every
+//    chunk (the persistent form) the two are as fast (50,000: 5.0 against 5.3,
+//    128,000: 10.0 against 9.2): T/4;
+//  * FP16 fields: never, the lane form keeps a cell in 48 registers and the quad
+//    form shared whole node pairs (12,000: 3.94 against 3.51);
+//  * the full equations have no quad form.
+__host__ __device__ constexpr uint32_t quad_limit(uint32_t T, bool f64_arithmetic, int field_dtype, bool full,
+                                                  bool every_chunk) {
+    if (full || field_dtype == GC_F16) return 0;
+    if (field_dtype == GC_F64) return every_chunk ? T / 4 : T;
+    return f64_arithmetic ? T / 8 : T / 4;
+}
 constexpr int kMaxMoments = 8192;
 constexpr int64_t kMaxRebirthSteps = 1 << 24;   // generations fit the 24 flag bits above GC_FLAG_GEN_SHIFT
 constexpr int kNumComp = 12;

@@ -14,14 +14,19 @@
 namespace gc {
 
 // Forms of the push (all bitwise identical in their results):
-//   kFormThroughput  one lane per particle, at most 256 registers; a gather that is not
-//                    cell-resident has two node pairs in registers at a time;
-//   kFormAllPairs    one lane per particle, all four pairs of a gather in flight;
-//   kFormQuad        four lanes per particle (an aligned quad): each lane interpolates three
-//                    of the twelve components of every gather (FP16 fields: loads one node
-//                    pair), the quad shares the results, all four run the rest of the step
-//                    on identical values, lane gl = 0 writes.
-enum { kFormThroughput = 0, kFormAllPairs = 1, kFormQuad = 2 };
+//   kFormLane      one lane per particle, at most 256 registers (two wavefronts per SIMD).
+//                  FP32 and FP16 fields: resident cells, every load of a gather in flight at
+//                  once.  FP64 fields and the full equations: every stencil loaded, two node
+//                  pairs of a gather in registers at a time;
+//   kFormAllPairs  FP64 fields and the full equations in the tail (kHasAllPairs): the same
+//                  with all four pairs of a gather in flight;
+//   kFormQuad      four lanes per particle (an aligned quad), FP32 and FP64 fields: each lane
+//                  keeps and interpolates three of the twelve components, the quad shares the
+//                  results, all four run the rest of the step on identical values, lane
+//                  gl = 0 writes.
+enum { kFormLane = 0, kFormAllPairs = 1, kFormQuad = 2 };
+template <int FDT, int MODE> constexpr bool kHasQuad = MODE != 2 && FDT != GC_F16;
+template <int FDT, int MODE> constexpr bool kHasAllPairs = MODE == 2 || FDT == GC_F64;
 
 // MODE 0: the reduced equations, no rebirth, centres at rest.  MODE 1: also
 // rebirth and scattering in the wind frame (Sect. 3 and 3.3); a separate
@@ -31,7 +36,7 @@ enum { kFormThroughput = 0, kFormAllPairs = 1, kFormQuad = 2 };
 // TAME: the field is tame (FieldDev::tame), so the gathers skip their
 // finiteness test (compiled out; a run-time branch around it measured slower,
 // and in the quad form no faster than the test).
-template <int PREC, int FDT, int MODE, int FORM = kFormThroughput, bool TAME = false>
+template <int PREC, int FDT, int MODE, int FORM = kFormLane, bool TAME = false>
 __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slot, uint32_t gl = 0) {
     constexpr bool EXT = MODE >= 1;
     constexpr bool FULL = MODE == 2;
@@ -100,9 +105,8 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
     // seldom any at X^n.  Per 64-step launch (FP64 on an FP32 256x128x256 field):
     // 2^20 electrons 2.40 -> 1.91 ms, 1,000 reborn electrons in the quad form
     // 2.09 -> 1.71 us a step; 300,007 in FP32 arithmetic 0.61 -> 0.39 ms.
-    constexpr bool kResident = !FULL && (FORM == kFormQuad ? FDT != GC_F16 : FDT != GC_F64);
-    using Cell = typename std::conditional<FORM == kFormQuad, QuadCell<FDT == GC_F16 ? GC_F32 : FDT>,
-                                           LaneCell<FDT == GC_F64 ? GC_F32 : FDT>>::type;
+    constexpr bool kResident = !FULL && (FORM == kFormQuad || FDT != GC_F64);
+    using Cell = typename std::conditional<FORM == kFormQuad, QuadCell<FDT>, LaneCell<FDT>>::type;
     CellPos<R> at;
     [[maybe_unused]] Cell cell;
     constexpr std::integral_constant<int, 0> first;
@@ -129,7 +133,6 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
             xbad = !xok;
             return ok;
         }
-        else if constexpr (FORM == kFormQuad) return gather_quad<FDT, R, TAME>(a.f, x, t, p, gl, g);
         else return gather<FDT, R, FORM == kFormAllPairs, TAME>(a.f, x, t, p, g);
     };
 
@@ -150,9 +153,9 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
         // follows runs on arbitrary values and is not committed.
         R Fn[4], Fs[4], vpn, vps;
         R px = (R)X0, pth = (R)X1, pph = (R)X2, pu = (R)X3;
-        auto rhs_at = [&](R x, R t, R u, R g[12], R xg[12], R F[4], R &vp) {
-            if constexpr (FULL) gc_rhs<R, true>(x, t, u, mu, qm, iqm, drift_free, g, F, vp, xg);
-            else gc_rhs<R>(x, t, u, mu, qm, iqm, drift_free, g, F, vp);
+        auto rhs_at = [&](R ir, R is, R u, R g[12], R xg[12], R F[4], R &vp) {
+            if constexpr (FULL) gc_rhs_at<R, true>(ir, is, u, mu, qm, iqm, drift_free, g, F, vp, xg);
+            else gc_rhs_at<R>(ir, is, u, mu, qm, iqm, drift_free, g, F, vp);
             if (EXT) vp = path_speed<R>(vp, g, vw);
         };
         if (rare((flags & kBack) != 0)) {
@@ -187,11 +190,12 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
             }
         }
         {   // X^n (or X^{n-1} of a bootstrap)
+            const R ir = rcp_nr(px), is = rcp_nr(sin_0_pi(pth));
             R g[12], xg[12];
             bool xbad;
             bad |= !value(first, twelve, px, pth, pph, g, xg, xbad);
             if (FULL) bad |= xbad;
-            rhs_at(px, pth, pu, g, xg, Fn, vpn);
+            rhs_at(ir, is, pu, g, xg, Fn, vpn);
         }
         bool go = true;
         if (rare((flags & GC_FLAG_BOOTSTRAP) != 0 && !bad)) {
@@ -218,12 +222,16 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
                 } else {
                     px = (R)(X0 + (A)d0); pth = (R)(X1 + (A)d1); pph = (R)(X2 + (A)d2); pu = (R)(X3 + (A)d3);
                 }
+                bad |= !seek(px, pth, pph);
+                // 1/r and 1/sin(th) while a new cell's nodes are on their way (the empty
+                // statement keeps the compiler from moving them to their use)
+                R ir = rcp_nr(px), is = rcp_nr(sin_0_pi(pth));
+                asm volatile("" : "+v"(ir), "+v"(is));
                 R g[12], xg[12];
                 bool xbad;
-                bad |= !seek(px, pth, pph);
                 bad |= !value(first, twelve, px, pth, pph, g, xg, xbad);
                 if (FULL) bad |= xbad;
-                rhs_at(px, pth, pu, g, xg, Fs, vps);
+                rhs_at(ir, is, pu, g, xg, Fs, vps);
             }
             if (rare(bad)) {
                 status = GC_NONFINITE;
@@ -337,17 +345,18 @@ __device__ __forceinline__ void push_grid(const PushArgs &a) {
     count_steps(a, taken);
 }
 
-// Throughput form: at most 256 registers per lane (two wavefronts per SIMD).
+// One lane per particle: at most 256 registers (two wavefronts per SIMD).
 template <int PREC, int FDT, int MODE, bool TAME>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_push(PushArgs a) {
-    push_grid<PREC, FDT, MODE, kFormThroughput, TAME>(a);
+    push_grid<PREC, FDT, MODE, kFormLane, TAME>(a);
 }
 
 // Latency forms, for fewer active particles than fill the machine: a
-// wavefront's step time is then its gathers' latency, set by the round trips
-// and by how many distinct cache lines its load instructions touch.  The
-// all-pairs form has each gather in one round trip; the quad form also spreads
-// the particles over four times as many wavefronts (and compute units).
+// wavefront's step time is then its chain of instructions and memory round
+// trips.  The all-pairs form (full equations) has each gather of an array in
+// one round trip; the quad form spreads the particles over four times as many
+// wavefronts (and compute units) and interpolates a quarter of the values per
+// lane (quad_limit).
 template <int PREC, int FDT, int MODE, bool TAME>
 __global__ __launch_bounds__(256) void k_push_allpairs(PushArgs a) {
     push_grid<PREC, FDT, MODE, kFormAllPairs, TAME>(a);
@@ -365,22 +374,22 @@ __global__ __launch_bounds__(256) void k_push_quad(PushArgs a) {
 // that a thinning population stays spread over the machine instead of
 // queueing behind few workgroups.
 //
-// With a tail threshold T = a.tail > 0 each chunk launches the throughput,
-// all-pairs and four-lanes-per-particle kernels in turn, and the live count on
-// the device (written by the reorder) selects the one that works, the others
-// returning at once: T and more, the throughput form; [T/kQuadShare, T), all
-// pairs (for the full equations, [0, T)); below it, four lanes per particle.  These
-// are the forms of the eager tail policy, chosen on the device so that a
-// captured graph follows the count without a host read-back.  Steps are
-// counted per form (a.steps_done + form).
+// With a tail threshold T = a.tail > 0 each chunk launches the one-lane kernel
+// and the tail kernels its instantiation has (all pairs, quad) in turn, and the
+// live count on the device (written by the reorder) selects the one that works,
+// the others returning at once: below quad_limit the quad form, from there to T
+// all pairs where that form exists, else one lane per particle.  The choice is
+// made on the device so that a captured graph follows the count without a host
+// read-back.  Steps are counted per form (a.steps_done + form), the one-lane
+// form's below T under [1].
 template <int PREC, int FDT, int MODE, int FORM, bool TAME = false>
 __device__ __forceinline__ void push_persistent(const PushArgs &a) {
     __shared__ uint32_t s_tile;
     const uint32_t n = *a.n_active;
     const uint32_t T = a.tail;
-    const uint32_t q4 = MODE == 2 ? 0u : T / kQuadShare;      // the full equations have no quad form
-    const uint32_t lo = FORM == kFormThroughput ? T : (FORM == kFormAllPairs ? q4 : 0u);
-    const uint32_t hi = FORM == kFormThroughput ? 0xFFFFFFFFu : (FORM == kFormAllPairs ? T : q4);
+    const uint32_t quad = quad_limit(T, PREC == GC_PREC_F64, FDT, MODE == 2, true);
+    const uint32_t lo = FORM == kFormQuad ? 0u : FORM == kFormLane && kHasAllPairs<FDT, MODE> ? T : quad;
+    const uint32_t hi = FORM == kFormLane ? 0xFFFFFFFFu : FORM == kFormAllPairs ? T : quad;
     if (n < lo || n >= hi) return;
     constexpr uint32_t G = FORM == kFormQuad ? 4 : 1;          // lanes per particle
     const uint32_t per = blockDim.x / G;                       // particles per workgroup round
@@ -398,12 +407,12 @@ __device__ __forceinline__ void push_persistent(const PushArgs &a) {
         for (uint32_t slot = t * tile + threadIdx.x / G; slot < end; slot += per)
             taken += advance_slot<PREC, FDT, MODE, FORM, TAME>(a, slot, threadIdx.x % G);
     }
-    count_steps(a.steps_done + FORM, taken);
+    count_steps(a.steps_done + (FORM == kFormLane && n < T ? kFormAllPairs : FORM), taken);
 }
 
 template <int PREC, int FDT, int MODE, bool TAME>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_push_persistent(PushArgs a) {
-    push_persistent<PREC, FDT, MODE, kFormThroughput, TAME>(a);
+    push_persistent<PREC, FDT, MODE, kFormLane, TAME>(a);
 }
 
 template <int PREC, int FDT, int MODE, bool TAME>
@@ -416,40 +425,45 @@ __global__ __launch_bounds__(256) void k_push_persistent_quad(PushArgs a) {
     push_persistent<PREC, FDT, MODE, kFormQuad, TAME>(a);
 }
 
-
 template <int PREC, int FDT, int MODE, bool TAME>
 static hipError_t launch_rt(const PushArgs &a, int block, bool persistent, int form, int grid_blocks, hipStream_t s,
                            LaunchEvents ev) {
     if (persistent) {
-        const bool quad = a.tail > 0 && MODE != 2;
+        constexpr bool kPairs = kHasAllPairs<FDT, MODE>, kQuad = kHasQuad<FDT, MODE>;
+        const bool tail = a.tail > 0;
         launch_timed((k_push_persistent<PREC, FDT, MODE, TAME>), dim3(grid_blocks), dim3(block), s, ev.start,
-                     a.tail > 0 ? nullptr : ev.stop, a);
-        if (a.tail > 0) {
-            launch_timed((k_push_persistent_allpairs<PREC, FDT, MODE, TAME>), dim3(grid_blocks), dim3(block), s, nullptr,
-                         quad ? nullptr : ev.stop, a);
-            if (quad) {  // 256-thread workgroups (64 particles per round), as the grid quad form
-                launch_timed((k_push_persistent_quad<PREC, FDT, MODE == 2 ? 1 : MODE, TAME>),
-                             dim3((uint32_t)grid_blocks * block / 256), dim3(256), s, nullptr, ev.stop, a);
-            }
-        }
-    } else {
-        const uint32_t nb = (a.n_slots + block - 1) / block;
-        if (nb == 0) {
-            if (ev.start) (void)hipEventRecord(ev.start, s);
-            if (ev.stop) (void)hipEventRecord(ev.stop, s);
+                     tail && (kPairs || kQuad) ? nullptr : ev.stop, a);
+        if constexpr (kPairs)
+            if (tail)
+                launch_timed((k_push_persistent_allpairs<PREC, FDT, MODE, TAME>), dim3(grid_blocks), dim3(block), s,
+                             nullptr, kQuad ? nullptr : ev.stop, a);
+        if constexpr (kQuad)
+            if (tail)   // 256-thread workgroups (64 particles per round), as the grid quad form
+                launch_timed((k_push_persistent_quad<PREC, FDT, MODE, TAME>), dim3((uint32_t)grid_blocks * block / 256),
+                             dim3(256), s, nullptr, ev.stop, a);
+        return hipGetLastError();
+    }
+    const uint32_t nb = (a.n_slots + block - 1) / block;
+    if (nb == 0) {
+        if (ev.start) (void)hipEventRecord(ev.start, s);
+        if (ev.stop) (void)hipEventRecord(ev.stop, s);
+        return hipGetLastError();
+    }
+    if constexpr (MODE == 2) {
+        if (form != kFormLane) {
+            launch_timed((k_push_allpairs<PREC, FDT, MODE, TAME>), dim3(nb), dim3(block), s, ev.start, ev.stop, a);
             return hipGetLastError();
         }
-        if (form == kFormQuad && MODE != 2) {
+    } else if constexpr (kHasQuad<FDT, MODE>) {
+        if (form == kFormQuad) {
             // 256-thread workgroups whatever the block size (64 particles each;
             // measured faster for this form than 64 threads)
             const uint32_t qb = (4 * a.n_slots + 255) / 256;
-            launch_timed((k_push_quad<PREC, FDT, MODE == 2 ? 1 : MODE, TAME>), dim3(qb), dim3(256), s, ev.start,
-                         ev.stop, a);
-        } else if (form != kFormThroughput)
-            launch_timed((k_push_allpairs<PREC, FDT, MODE, TAME>), dim3(nb), dim3(block), s, ev.start, ev.stop, a);
-        else
-            launch_timed((k_push<PREC, FDT, MODE, TAME>), dim3(nb), dim3(block), s, ev.start, ev.stop, a);
+            launch_timed((k_push_quad<PREC, FDT, MODE, TAME>), dim3(qb), dim3(256), s, ev.start, ev.stop, a);
+            return hipGetLastError();
+        }
     }
+    launch_timed((k_push<PREC, FDT, MODE, TAME>), dim3(nb), dim3(block), s, ev.start, ev.stop, a);
     return hipGetLastError();
 }
 
