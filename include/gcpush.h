@@ -419,7 +419,7 @@ gc_status gc_mlp_train_step(gc_ctx *ctx, const double *pts, const double *tgt, i
  * gradient and update, with its training workspace (activations,
  * pre-activations, output gradients, split-K and column-sum partials, loss
  * partials) in a static device array of the library instead of memory the
- * context allocates.  The array holds 24.2 MiB, enough for n_pairs <= 2048,
+ * context allocates.  The array holds 14.0 MiB, enough for n_pairs <= 2048,
  * and each device the library runs on keeps its own copy until the process
  * ends.  The call allocates nothing (no hipMalloc, hipFree or allocator
  * callback); it reads the loss back and waits, like gc_mlp_train_step.

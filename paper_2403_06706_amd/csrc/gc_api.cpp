@@ -29,17 +29,9 @@ struct GraphKey {
     gc_options opt{};
 };
 
-// Training workspace of the neural field for some number of rows (carve_ws).
-struct TrainWs {
-    __bf16 *H = nullptr, *dZ = nullptr;                  // H: activations H0..H6, [7][rows][128]
-    float *Z = nullptr, *Y = nullptr, *dY = nullptr;     // Z: pre-activations [6][rows][128]
-    float *dH = nullptr, *part = nullptr;                // part: split-K and column-sum partials
-    double *loss_part = nullptr;
-};
-
 // Neural field: FP32 master parameters (padded device layout), Adam moments,
 // gradient and the BF16 copies used by the matrix-core products; training
-// workspace sized for ws_rows rows.
+// workspace sized for ws_pairs pairs.
 struct MlpState {
     bool set = false;
     MlpArgs args{};
@@ -48,8 +40,8 @@ struct MlpState {
     __bf16 *W = nullptr, *WT = nullptr, *Wo = nullptr;   // natural order (training)
     __bf16 *We = nullptr, *Woe = nullptr;                 // evaluation order (mlp_perm)
     void *ws = nullptr;
-    int64_t ws_rows = 0;
-    TrainWs w{};                                         // carved from ws
+    int64_t ws_pairs = 0;
+    TrainBufs w{};                                       // carved from ws
 };
 
 struct gc_ctx {
@@ -94,6 +86,7 @@ struct gc_ctx {
     unsigned long long *steps = nullptr;       // [kPushForms] active particle-steps by push form
     uint32_t *log = nullptr;
     volatile uint32_t *count_host = nullptr;   // live count of the latest completed reorder (pinned)
+    volatile double *loss_host = nullptr;      // loss of the last training step (same pinned block)
     bool capturing = false;
     int tail_skip = 0;                         // reorders still to skip in the tail
     hipEvent_t ahead[4] = {nullptr, nullptr, nullptr, nullptr};   // ends of the last chunks issued
@@ -661,6 +654,7 @@ gc_status gc_create(gc_ctx **out, const gc_options *opt) {
     void *pinned = nullptr;
     HIPCHK(hipHostMalloc(&pinned, 64, hipHostMallocCoherent));
     ctx->count_host = static_cast<volatile uint32_t *>(pinned);
+    ctx->loss_host = reinterpret_cast<volatile double *>(static_cast<char *>(pinned) + 32);
     *ctx->count_host = 0xFFFFFFFFu;
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return GC_OK;
@@ -1277,10 +1271,6 @@ namespace {
 constexpr int kUserParams = GC_MLP_PARAMS;             // W | c | W_o[6][128] | c_o[6]
 constexpr int kUserOffWo = kMlpOffWo, kUserOffCo = kMlpOffWo + kMlpOut * kMlpWidth;
 static_assert(kUserOffCo + kMlpOut == kUserParams, "GC_MLP_PARAMS does not match the network shape");
-constexpr int kTrainGroups = 128;                     // most row groups of the split-K weight gradients
-constexpr int kRowsPerGroup = 128;
-constexpr int kLossBlocks = 512;
-
 void to_device_layout(const float *u, std::vector<float> &d) {
     d.assign(kMlpParams, 0.0f);
     if (!u) return;
@@ -1297,46 +1287,36 @@ void to_user_layout(const std::vector<float> &d, float *u) {
 
 constexpr size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// Partials of the training step for R rows: the split-K weight gradients
-// (row groups, at most kTrainGroups), and the column sums of the output layer
-// (one block per kColRows rows, plus the summed block).
-constexpr size_t ws_part_floats(size_t R, size_t wgrad_groups) {
-    return std::max<size_t>(wgrad_groups * kMlpWidth * kMlpWidth,
-                            (size_t)(mlp_col_groups((int)std::min<size_t>(R, 1u << 30)) + 1) *
-                                (kMlpOut * kMlpWidth + kMlpOut));
+// Bytes of the training workspace for n pairs; carve_ws cuts it up.
+constexpr size_t ws_tiles(int64_t n) { return (size_t)mlp_train_blocks(n) * kMlpDepth * kMlpWidth * kTrainRows * 2; }
+constexpr size_t kWsPart = (size_t)kMlpDepth * 4 * kMlpWidth * kMlpWidth * 4;
+constexpr size_t ws_sums(int64_t n) { return (size_t)mlp_train_blocks(n) * kTrainSums * 4; }
+constexpr size_t ws_bytes(int64_t n) {
+    return 2 * align256(ws_tiles(n)) + align256(kWsPart) + align256(ws_sums(n)) + align256((size_t)2 * n * kMlpOut * 4) +
+           align256((size_t)mlp_train_blocks(n) * 8);
 }
 
-// Bytes of the training workspace for R rows; with base, also carve it.
-constexpr size_t ws_bytes(size_t R, size_t part) {
-    return align256(7 * R * kMlpWidth * 2) + align256(R * kMlpWidth * 2) + align256(6 * R * kMlpWidth * 4) +
-           2 * align256(R * kMlpOut * 4) + align256(R * kMlpWidth * 4) + align256(part * 4) +
-           align256(kLossBlocks * 8);
+void carve_ws(char *c, int64_t n, TrainBufs &w) {
+    w.HT = reinterpret_cast<__bf16 *>(c); c += align256(ws_tiles(n));
+    w.DT = reinterpret_cast<__bf16 *>(c); c += align256(ws_tiles(n));
+    w.part = reinterpret_cast<float *>(c); c += align256(kWsPart);
+    w.sums = reinterpret_cast<float *>(c); c += align256(ws_sums(n));
+    w.Y = reinterpret_cast<float *>(c); c += align256((size_t)2 * n * kMlpOut * 4);
+    w.loss = reinterpret_cast<double *>(c);
 }
 
-void carve_ws(char *c, size_t R, size_t part, TrainWs &w) {
-    w.H = reinterpret_cast<__bf16 *>(c); c += align256(7 * R * kMlpWidth * 2);
-    w.dZ = reinterpret_cast<__bf16 *>(c); c += align256(R * kMlpWidth * 2);
-    w.Z = reinterpret_cast<float *>(c); c += align256(6 * R * kMlpWidth * 4);
-    w.Y = reinterpret_cast<float *>(c); c += align256(R * kMlpOut * 4);
-    w.dY = reinterpret_cast<float *>(c); c += align256(R * kMlpOut * 4);
-    w.dH = reinterpret_cast<float *>(c); c += align256(R * kMlpWidth * 4);
-    w.part = reinterpret_cast<float *>(c); c += align256(part * 4);
-    w.loss_part = reinterpret_cast<double *>(c);
-}
-
-gc_status mlp_workspace(gc_ctx *ctx, int64_t rows) {
+// (the workspace of n pairs also holds every smaller step: no part of it shrinks with n)
+gc_status mlp_workspace(gc_ctx *ctx, int64_t pairs) {
     MlpState &m = ctx->mlp;
-    if (rows <= m.ws_rows) return GC_OK;
-    const int64_t cap = std::max<int64_t>(rows, 2 * m.ws_rows);
-    const size_t R = (size_t)cap;
-    const size_t part = ws_part_floats(R, kTrainGroups);
+    if (pairs <= m.ws_pairs) return GC_OK;
+    const int64_t cap = std::max<int64_t>(pairs, 2 * m.ws_pairs);
     void *mem = nullptr;
-    if (dalloc(ctx, (void **)&mem, ws_bytes(R, part)) != hipSuccess)
-        return fail(ctx, GC_ENOMEM, "cannot allocate the training workspace for %lld rows", (long long)cap);
+    if (dalloc(ctx, (void **)&mem, ws_bytes(cap)) != hipSuccess)
+        return fail(ctx, GC_ENOMEM, "cannot allocate the training workspace for %lld rows", (long long)(2 * cap));
     if (m.ws) dfree(ctx, m.ws);
     m.ws = mem;
-    m.ws_rows = cap;
-    carve_ws(static_cast<char *>(mem), R, part, m.w);
+    m.ws_pairs = cap;
+    carve_ws(static_cast<char *>(mem), cap, m.w);
     return GC_OK;
 }
 
@@ -1348,9 +1328,7 @@ gc_status mlp_workspace(gc_ctx *ctx, int64_t rows) {
 // uses the device address read once per device with hipGetSymbolAddress.
 // ---------------------------------------------------------------------------
 constexpr int64_t kStaticPairs = 2048;
-constexpr size_t kStaticRows = 2 * kStaticPairs;
-constexpr size_t kStaticPart = ws_part_floats(kStaticRows, std::min<size_t>(kTrainGroups, kStaticRows / kRowsPerGroup));
-constexpr size_t kStaticBytes = ws_bytes(kStaticRows, kStaticPart);
+constexpr size_t kStaticBytes = ws_bytes(kStaticPairs);
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 constexpr int kMaxDevices = 64;
@@ -1490,45 +1468,28 @@ gc_status check_train(gc_ctx *ctx, const double *pts, const double *tgt, int64_t
 }
 
 // Forward, loss, backward and the optional Adam update on the workspace w
-// (which holds at least 2 n_pairs rows); the loss partials are read back.
+// (which holds n_pairs pairs); the loss comes back in pinned host memory.
 gc_status train_step(gc_ctx *ctx, const double *pts, const double *tgt, int64_t n_pairs, const gc_mlp_train_opts *o,
-                     double *loss, const TrainWs &w) {
+                     double *loss, const TrainBufs &w) {
     MlpState &m = ctx->mlp;
     hipStream_t s = ctx->stream;
-    const int rows = (int)(2 * n_pairs);
-    const size_t RW = (size_t)rows * kMlpWidth, WW = (size_t)kMlpWidth * kMlpWidth;
-    // forward: H0 = features, H_{l+1} = silu(H_l W_l^T + c_l), Y = H6 W_o^T + c_o
-    HIPCHK(mlp_launch_features(m.args, pts, rows, w.H, s));
-    for (int l = 0; l < kMlpDepth; ++l)
-        HIPCHK(mlp_launch_forward_layer(w.H + l * RW, m.W + l * WW, m.p + kMlpOffC + l * kMlpWidth, rows, w.Z + l * RW,
-                                        w.H + (l + 1) * RW, s));
-    HIPCHK(mlp_launch_output(w.H + kMlpDepth * RW, m.Wo, m.p + kMlpOffCo, rows, w.Y, s));
-    // loss and its gradient with respect to the outputs
     MlpLoss L{};
     for (int c = 0; c < kMlpOut; ++c) L.wc[c] = o->wc[c];
     L.beta = o->beta_pair;
-    const int lb = (int)std::min<int64_t>(kLossBlocks, (n_pairs + 255) / 256);
-    HIPCHK(mlp_launch_loss(m.args, pts, tgt, w.Y, (int)n_pairs, L, w.dY, w.loss_part, lb, s));
-    // backward; weight-gradient products split over row groups of about kRowsPerGroup rows
-    const int groups = std::max(1, std::min(kTrainGroups, rows / kRowsPerGroup));
-    HIPCHK(mlp_launch_out_grad(w.dY, w.H + kMlpDepth * RW, rows, w.part, m.g + kMlpOffWo, m.g + kMlpOffCo, s));
-    HIPCHK(mlp_launch_out_back(w.dY, m.p + kMlpOffWo, rows, w.dH, s));
-    for (int l = kMlpDepth - 1; l >= 0; --l) {
-        HIPCHK(mlp_launch_dz(w.dH, w.Z + l * RW, rows, w.dZ, w.part, m.g + kMlpOffC + l * kMlpWidth, s));
-        HIPCHK(mlp_launch_wgrad(w.dZ, w.H + l * RW, rows, groups, w.part, m.g + kMlpOffW + l * WW, s));
-        if (l > 0) HIPCHK(mlp_launch_backward_data(w.dZ, m.WT + l * WW, rows, w.dH, s));
+    const TrainNet net{m.p, m.mo, m.ve, m.g, m.p + kMlpOffC, m.p + kMlpOffCo, m.p + kMlpOffWo, m.W, m.WT, m.Wo, m.We, m.Woe};
+    AdamArgs a{};
+    a.apply = o->apply != 0;
+    if (a.apply) {
+        a.lr = (float)o->lr;
+        a.b1 = (float)o->beta1;
+        a.b2 = (float)o->beta2;
+        a.eps = (float)o->eps;
+        a.c1 = 1.0f - powf(a.b1, (float)o->step);
+        a.c2 = 1.0f - powf(a.b2, (float)o->step);
     }
-    if (o->apply) {
-        HIPCHK(mlp_launch_adam(m.p, m.mo, m.ve, m.g, kMlpParams, (float)o->lr, (float)o->beta1, (float)o->beta2,
-                               (float)o->eps, o->step, s));
-        HIPCHK(mlp_launch_refresh(m.p, m.W, m.WT, m.Wo, m.We, m.Woe, s));
-    }
-    double lp[kLossBlocks];
-    HIPCHK(hipMemcpyAsync(lp, w.loss_part, lb * sizeof(double), hipMemcpyDeviceToHost, s));
+    HIPCHK(mlp_launch_train(m.args, net, pts, tgt, (int)n_pairs, L, a, w, ctx->loss_host, s));
     HIPCHK(hipStreamSynchronize(s));
-    double sum = 0.0;
-    for (int i = 0; i < lb; ++i) sum += lp[i];
-    if (loss) *loss = sum;
+    if (loss) *loss = *ctx->loss_host;
     return GC_OK;
 }
 
@@ -1542,7 +1503,7 @@ gc_status gc_mlp_train_step(gc_ctx *ctx, const double *pts, const double *tgt, i
     gc_status st = check_train(ctx, pts, tgt, n_pairs, o, 1 << 26);
     if (st != GC_OK) return st;
     HIPCHK(hipSetDevice(ctx->opt.device));
-    st = mlp_workspace(ctx, 2 * n_pairs);
+    st = mlp_workspace(ctx, n_pairs);
     if (st != GC_OK) return st;
     return train_step(ctx, pts, tgt, n_pairs, o, loss, ctx->mlp.w);
 }
@@ -1558,8 +1519,8 @@ gc_status gc_mlp_train_step_noalloc(gc_ctx *ctx, const double *pts, const double
     if (!g_scratch_ptr[dev])
         return fail(ctx, GC_EDEVICE, "static workspace of device %d: %s", dev, hipGetErrorString(g_scratch_err[dev]));
     HIPCHK(hipSetDevice(dev));
-    TrainWs w{};
-    carve_ws(static_cast<char *>(g_scratch_ptr[dev]), kStaticRows, kStaticPart, w);
+    TrainBufs w{};
+    carve_ws(static_cast<char *>(g_scratch_ptr[dev]), kStaticPairs, w);
     return train_step(ctx, pts, tgt, n_pairs, o, loss, w);
 }
 

@@ -11,237 +11,385 @@
 namespace gc {
 
 // ---------------------------------------------------------------------------
-// Features of training rows (no tangents): H0[row][128] bf16.
-// pts: SoA r[n], th[n], ph[n].
+// Training step in four kernels:
+//   k_mlp_train<false>  features and forward of a block of 64 rows: the outputs;
+//   k_mlp_train<true>   loss and output gradient, the forward again (its
+//                       pre-activations stay in registers) and the backward pass
+//                       to every dZ, with the block's bias and output-layer sums;
+//   k_mlp_wgrad         the hidden layers' weight gradients;
+//   k_mlp_update        the remaining sums, Adam, the BF16 copies, the loss.
+// The loss couples rows i and n + i of different blocks, hence two forward
+// passes: the second costs less than writing the pre-activations and reading
+// them back (50 MB at 16,384 rows).  A step of that size is 10 GFLOP, 8 us at the
+// rate of a large BF16 product; as one kernel per layer and pass (43 launches,
+// every activation, pre-activation and gradient through memory) it took 0.78 ms,
+// of which 0.66 ms in kernels; now 24 + 48 + 35 + 5 us.
+//
+// Activations H_0..H_5 and gradients dZ_1..dZ_6 go to memory once, in BF16,
+// transposed in tiles [block][layer][128 columns][64 rows]: k_mlp_wgrad sums over
+// rows and reads its operands, eight rows of a column, straight from there.  Rows
+// past the last repeat it with a zero gradient.  Every FP32 sum over rows is taken
+// in one order (blocks of 64 rows: even rows, odd rows; four interleaved chains
+// over the blocks; weight gradients: groups of mlp_train_chunk rows, four
+// interleaved chains over the groups), whatever the launch shapes.
 // ---------------------------------------------------------------------------
-__global__ void k_mlp_features(MlpArgs m, const double *pts, int n, __bf16 *H0) {
-    const int row = blockIdx.x * blockDim.y + threadIdx.y;   // blockDim = (64, 4): 64 lanes share a row
-    if (row >= n) return;
-    const int j = threadIdx.x;                               // phase index
-    const float rt = (float)((pts[row] - (double)m.r_min) * (double)m.inv_rspan);
-    const float tt = (float)(pts[n + row] * 0.3183098861837907);
-    const float ph = (float)pts[2 * n + row];
-    const float psi = 6.283185307179586f * (m.fa[j] * rt + m.fb[j] * tt) + m.fn[j] * ph;
-    float sn, cs;
-    __sincosf(psi, &sn, &cs);
-    H0[(size_t)row * kMlpWidth + 2 * j] = (__bf16)sn;
-    H0[(size_t)row * kMlpWidth + 2 * j + 1] = (__bf16)cs;
-}
+constexpr int kTrainThreads = 512;
+constexpr int kTrainPitch = kMlpWidth + 8;      // LDS row of a 64 x 128 BF16 matrix: 272 bytes, four banks a row
+constexpr size_t kTileT = (size_t)kMlpWidth * kTrainRows;   // elements of a transposed tile
 
-// ---------------------------------------------------------------------------
-// C[row][n] = sum_k A[row][k] Bt[n][k] for 32 rows per wavefront, NT 32-wide
-// column tiles.  MODE 0 (forward hidden layer): Z = C + bias, store Z (fp32)
-// and silu(Z) (bf16).  MODE 1 (backward data): store C (fp32).  MODE 2
-// (output layer): store C + bias for the first kMlpOut columns (fp32, n x 6).
-// ---------------------------------------------------------------------------
-template <int MODE, int NT>
-__global__ __launch_bounds__(256) void k_mlp_gemm(const __bf16 *A, const __bf16 *Bt, const float *bias, int rows,
-                                                  float *Cout, __bf16 *Hout) {
-    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = l >> 5, mrow = l & 31;
-    const int row0 = (blockIdx.x * 4 + wave) * 32;
-    if (row0 >= rows) return;                                   // whole wavefront idle
-    floatx16 acc[NT];
+// A wavefront owns one 32 x 32 tile of every 64 x 128 matrix (row half w / 4,
+// columns 32 (w % 4)..): its slice of the weights comes from L2 straight into
+// registers, one layer ahead; the pre-activations of its tile stay there (96
+// registers) until the backward pass needs their slopes; the matrix itself goes
+// round through LDS for the next product's rows.  v_mfma_f32_32x32x16_bf16, K in
+// order.  Bound by the chain of 11 products, each an LDS round trip, eight
+// dependent matrix instructions and a barrier.
+template <bool kBack>
+__global__ __launch_bounds__(kTrainThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void k_mlp_train(MlpArgs m, TrainNet net, const double *pts, const double *tgt, int npair, MlpLoss L, float *Y,
+                 __bf16 *HT, __bf16 *DT, float *sums, double *loss_part) {
+    __shared__ __bf16 X[2][kTrainRows * kTrainPitch];
+    __shared__ float dYs[kBack ? kTrainRows : 1][8];
+    __shared__ float Gs[kBack ? kTrainRows * kMlpWidth : 1], Ss[kBack ? kTrainRows * kMlpWidth : 1];   // dH, silu'(Z)
+    __shared__ double red[kBack ? kTrainRows * kMlpOut : 1];
+    __shared__ float odd[kBack ? kMlpOut * kMlpWidth + kMlpOut : 1];
+    const int tid = threadIdx.x, l = tid & 63, w = tid >> 6, blk = blockIdx.x;
+    const int half = l >> 5, lane = l & 31, rt = w >> 2, col = 32 * (w & 3) + lane;
+    const int rows = 2 * npair, row0 = blk * kTrainRows;
+    // operand fragment s of a matrix with rows of 128 (row r, elements 16 s + 8 half ..)
+    auto frag = [&](const __bf16 *base, size_t pitch, int r, int s) {
+        return *reinterpret_cast<const bf16x8 *>(base + (size_t)r * pitch + 16 * s + 8 * half);
+    };
+    // row of accumulator element j within the block
+    auto row_of = [&](int j) { return 32 * rt + (j / 4) * 8 + half * 4 + (j % 4); };
+    auto tile_t = [&](__bf16 *base, int layer) { return base + ((size_t)blk * kMlpDepth + layer) * kTileT; };
+    // a tile in BF16: into LDS by rows, and into its transposed tile
+    auto put = [&](const float v[16], __bf16 *lds, __bf16 *T) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = floatx16{};
-    const int arow = row0 + mrow;
-    for (int s = 0; s < 8; ++s) {
-        bf16x8 a = {};
-        if (arow < rows) a = *reinterpret_cast<const bf16x8 *>(A + (size_t)arow * kMlpWidth + 16 * s + 8 * half);
+        for (int q = 0; q < 4; ++q) {
+            __bf16 b[4];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const bf16x8 b = *reinterpret_cast<const bf16x8 *>(Bt + (size_t)(32 * nt + mrow) * kMlpWidth + 16 * s + 8 * half);
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[nt], 0, 0, 0);
+            for (int e = 0; e < 4; ++e) b[e] = (__bf16)v[4 * q + e];
+            if (lds)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) lds[row_of(4 * q + e) * kTrainPitch + col] = b[e];
+            if (T) __builtin_memcpy(T + (size_t)col * kTrainRows + row_of(4 * q), b, 8);
+        }
+    };
+    bf16x8 bw[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) bw[s] = frag(net.W, kMlpWidth, col, s);
+    if constexpr (kBack) {
+        if (tid < kTrainRows * kMlpOut) {               // loss and dY: one (row, output) each
+            const int rl = tid / kMlpOut, c = tid % kMlpOut, r = row0 + rl, i = r < npair ? r : r - npair;
+            double part = 0.0;
+            float d = 0.0f;
+            if (r < rows) {
+                const double e1 = (double)m.scale[c] * pow((double)m.r_ref / pts[i], (double)m.power[c]);
+                const double e2 = (double)m.scale[c] * pow((double)m.r_ref / pts[npair + i], (double)m.power[c]);
+                const double t1 = tgt[(size_t)i * kMlpOut + c] / e1, t2 = tgt[(size_t)(npair + i) * kMlpOut + c] / e2;
+                const double y1 = Y[(size_t)i * kMlpOut + c], y2 = Y[(size_t)(npair + i) * kMlpOut + c];
+                const double d1 = y1 - t1, d12 = (y2 - y1) - (t2 - t1);
+                if (r < npair) {
+                    part = L.wc[c] * (d1 * d1 + L.beta * d12 * d12);
+                    d = (float)((2.0 * L.wc[c] * d1 - 2.0 * L.beta * L.wc[c] * d12) / npair);
+                } else {
+                    d = (float)(2.0 * L.beta * L.wc[c] * d12 / npair);
+                }
+            }
+            dYs[rl][c] = d;
+            red[tid] = part;
         }
     }
+    {   // features: phase tid % 64, eight rows
+        const int j = l, r0 = 8 * w;
+        __bf16 sc[2][8];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int n = 32 * nt + mrow;
+        for (int e = 0; e < 8; ++e) {
+            const int r = r0 + e, row = min(row0 + r, rows - 1);
+            const float rt_ = (float)((pts[row] - (double)m.r_min) * (double)m.inv_rspan);
+            const float tt = (float)(pts[(size_t)rows + row] * 0.3183098861837907);
+            const float ph = (float)pts[2 * (size_t)rows + row];
+            const float psi = 6.283185307179586f * (m.fa[j] * rt_ + m.fb[j] * tt) + m.fn[j] * ph;
+            float sn, cs;
+            __sincosf(psi, &sn, &cs);
+            sc[0][e] = (__bf16)sn;
+            sc[1][e] = (__bf16)cs;
+            X[0][r * kTrainPitch + 2 * j] = sc[0][e];
+            X[0][r * kTrainPitch + 2 * j + 1] = sc[1][e];
+        }
+        if constexpr (kBack) {
+            __bf16 *T = tile_t(HT, 0);
+            __builtin_memcpy(T + (size_t)(2 * j) * kTrainRows + r0, sc[0], 16);
+            __builtin_memcpy(T + (size_t)(2 * j + 1) * kTrainRows + r0, sc[1], 16);
+        }
+    }
+    float Z[kBack ? kMlpDepth : 1][16];
+#pragma unroll
+    for (int k = 0; k < kMlpDepth; ++k) {
+        __syncthreads();                                // X[k & 1] holds H_k
+        floatx16 acc = {};
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(X[k & 1], kTrainPitch, 32 * rt + lane, s), bw[s], acc, 0, 0, 0);
+        const float bias = net.c[k * kMlpWidth + col];
+        // the next product's weights: the next layer's; then the output layer's (one
+        // 32-row tile), or the first of the backward pass
+        const __bf16 *nw = k + 1 < kMlpDepth ? net.W + (size_t)(k + 1) * kMlpWidth * kMlpWidth
+                           : kBack           ? net.WT + (size_t)k * kMlpWidth * kMlpWidth
+                                             : net.Wo;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) bw[s] = frag(nw, kMlpWidth, k + 1 < kMlpDepth || kBack ? col : lane, s);
+        float h[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int row = row0 + (j / 4) * 8 + half * 4 + (j % 4);
-            if (row >= rows) continue;
-            if (MODE == 0) {
-                const float z = acc[nt][j] + bias[n];
-                Cout[(size_t)row * kMlpWidth + n] = z;
-                Hout[(size_t)row * kMlpWidth + n] = (__bf16)silu_f(z);
-            } else if (MODE == 1) {
-                Cout[(size_t)row * kMlpWidth + n] = acc[nt][j];
-            } else if (n < kMlpOut) {
-                Cout[(size_t)row * kMlpOut + n] = acc[nt][j] + bias[n];
+            const float z = acc[j] + bias;
+            if constexpr (kBack) Z[k][j] = z;
+            h[j] = silu_f(z);
+        }
+        put(h, X[(k + 1) & 1], kBack && k + 1 < kMlpDepth ? tile_t(HT, k + 1) : nullptr);
+    }
+    __syncthreads();                                    // X[0] holds H_6
+    if constexpr (!kBack) {
+        if ((w & 3) == 0) {                             // outputs: 32 padded columns, two wavefronts
+            floatx16 acc = {};
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(X[0], kTrainPitch, 32 * rt + lane, s), bw[s], acc, 0, 0, 0);
+            if (lane < kMlpOut) {
+                const float co = net.co[lane];
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (row0 + row_of(j) < rows) Y[(size_t)(row0 + row_of(j)) * kMlpOut + lane] = acc[j] + co;
             }
         }
+        return;
     }
-}
-
-// ---------------------------------------------------------------------------
-// Weight gradient, split over row chunks: P[g][n][k] = sum_{rows of chunk g} D[r][n] H[r][k].
-// Each workgroup stages 16 rows of D and H transposed in LDS, so that the
-// MFMA operands (8 consecutive rows of one column) are 16-byte LDS reads.
-// ---------------------------------------------------------------------------
-constexpr int kWgRow = 16 + 8;   // padded LDS row (bf16) of the transposed tiles
-
-__global__ __launch_bounds__(256) void k_mlp_wgrad(const __bf16 *D, const __bf16 *H, int rows, int chunk,
-                                                   float *partial) {
-    __shared__ __bf16 Dt[kMlpWidth * kWgRow];
-    __shared__ __bf16 Ht[kMlpWidth * kWgRow];
-    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = l >> 5, mrow = l & 31;
-    const int r_begin = blockIdx.x * chunk, r_end = min(rows, r_begin + chunk);
-    floatx16 acc[4];
+    // column sums: thread (parity, k) adds the rows of its parity in order
+    const int par = tid >> 7, kk = tid & (kMlpWidth - 1);
+    float *out = sums + (size_t)blk * kTrainSums;       // bias gradients [6][128], dWo [6][128], dco [6]
+    float ws[kMlpOut] = {}, wb[kMlpOut] = {};
+    if (par < 2) {                                      // output layer: dWo[c][k] = sum_r dY[r][c] H6[r][k], dco
+        for (int r = par; r < kTrainRows; r += 2) {
+            const float h = (float)X[0][r * kTrainPitch + kk];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = floatx16{};
-    for (int r0 = r_begin; r0 < r_end; r0 += 16) {
-        // stage 16 x 128 of D and H, transposed: Xt[col][row]
-        for (int e = threadIdx.x; e < 16 * kMlpWidth; e += 256) {
-            const int rr = e / kMlpWidth, cc = e % kMlpWidth;
-            const int r = r0 + rr;
-            const __bf16 zero = (__bf16)0.0f;
-            Dt[cc * kWgRow + rr] = r < r_end ? D[(size_t)r * kMlpWidth + cc] : zero;
-            Ht[cc * kWgRow + rr] = r < r_end ? H[(size_t)r * kMlpWidth + cc] : zero;
+            for (int c = 0; c < kMlpOut; ++c) {
+                ws[c] = fmaf(dYs[r][c], h, ws[c]);
+                wb[c] += dYs[r][c];
+            }
         }
-        __syncthreads();
-        // A[m = n-unit][k = row] = D[row][32 wave + m];  B[k = row][n = k-unit] = H[row][32 nt + n]
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(Dt + (32 * wave + mrow) * kWgRow + 8 * half);
+        if (par == 1) {
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const bf16x8 b = *reinterpret_cast<const bf16x8 *>(Ht + (32 * nt + mrow) * kWgRow + 8 * half);
-            acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[nt], 0, 0, 0);
+            for (int c = 0; c < kMlpOut; ++c) {
+                odd[c * kMlpWidth + kk] = ws[c];
+                if (kk == 0) odd[kMlpOut * kMlpWidth + c] = wb[c];
+            }
         }
-        __syncthreads();
+    } else if (w == 7) {                                // the block's loss
+        double v = 0.0;
+        for (int q = l; q < kTrainRows * kMlpOut; q += 64) v += red[q];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if (l == 0) loss_part[blk] = v / npair;
     }
-    float *P = partial + (size_t)blockIdx.x * kMlpWidth * kMlpWidth;
+    float dH[16];
+    {   // dH6 = dY Wo (K = 6: plain FP32)
+        float wo[kMlpOut];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+        for (int c = 0; c < kMlpOut; ++c) wo[c] = net.Wo_master[c * kMlpWidth + col];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int nrow = 32 * wave + (j / 4) * 8 + half * 4 + (j % 4);
-            P[nrow * kMlpWidth + 32 * nt + mrow] = acc[nt][j];
-        }
-}
-
-// out[i] (+)= sum_g partial[g][i], i < count (deterministic order; four
-// independent partial sums keep several loads in flight)
-__global__ void k_sum_partials(const float *partial, int groups, int count, float *out, int accumulate) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    int g = 0;
-    for (; g + 4 <= groups; g += 4)
+            dH[j] = 0.0f;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s[u] += partial[(size_t)(g + u) * count + i];
-    for (; g < groups; ++g) s[0] += partial[(size_t)g * count + i];
-    const float t = (s[0] + s[1]) + (s[2] + s[3]);
-    out[i] = accumulate ? out[i] + t : t;
-}
-
-// ---------------------------------------------------------------------------
-// Loss of the normalized outputs at paired points (rows 0..N-1 and N..2N-1)
-// and its gradient with respect to the outputs.  Per-block partial sums.
-// ---------------------------------------------------------------------------
-__global__ void k_mlp_loss(MlpArgs m, const double *pts, const double *tgt, const float *Y, int npair, MlpLoss L,
-                           float *dY, double *loss_partial) {
-    __shared__ double red[256];
-    double acc = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < npair; i += gridDim.x * blockDim.x) {
-        const double r1 = pts[i], r2 = pts[npair + i];
-        for (int c = 0; c < kMlpOut; ++c) {
-            const double e1 = (double)m.scale[c] * pow((double)m.r_ref / r1, (double)m.power[c]);
-            const double e2 = (double)m.scale[c] * pow((double)m.r_ref / r2, (double)m.power[c]);
-            const double t1 = tgt[(size_t)i * kMlpOut + c] / e1, t2 = tgt[(size_t)(npair + i) * kMlpOut + c] / e2;
-            const double y1 = Y[(size_t)i * kMlpOut + c], y2 = Y[(size_t)(npair + i) * kMlpOut + c];
-            const double d1 = y1 - t1, d12 = (y2 - y1) - (t2 - t1);
-            acc += L.wc[c] * (d1 * d1 + L.beta * d12 * d12);
-            dY[(size_t)i * kMlpOut + c] = (float)((2.0 * L.wc[c] * d1 - 2.0 * L.beta * L.wc[c] * d12) / npair);
-            dY[(size_t)(npair + i) * kMlpOut + c] = (float)(2.0 * L.beta * L.wc[c] * d12 / npair);
+            for (int c = 0; c < kMlpOut; ++c) dH[j] = fmaf(dYs[row_of(j)][c], wo[c], dH[j]);
         }
     }
-    red[threadIdx.x] = acc;
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    if (par == 0) {
+        constexpr int o = kMlpDepth * kMlpWidth;
+#pragma unroll
+        for (int c = 0; c < kMlpOut; ++c) {
+            out[o + c * kMlpWidth + kk] = ws[c] + odd[c * kMlpWidth + kk];
+            if (kk == 0) out[o + kMlpOut * kMlpWidth + c] = wb[c] + odd[kMlpOut * kMlpWidth + c];
+        }
+    }
+#pragma unroll
+    for (int k = kMlpDepth - 1; k >= 0; --k) {
+        // X[(k + 1) & 1], Gs and Ss are free: their last readers passed a barrier
+        float dz[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const float slope = dsilu_f(Z[k][j]);
+            dz[j] = dH[j] * slope;
+            Gs[row_of(j) * kMlpWidth + col] = dH[j];
+            Ss[row_of(j) * kMlpWidth + col] = slope;
+        }
+        put(dz, k > 0 ? X[(k + 1) & 1] : nullptr, tile_t(DT, k));
+        __syncthreads();
+        if (k > 0) {
+            floatx16 acc = {};
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(X[(k + 1) & 1], kTrainPitch, 32 * rt + lane, s), bw[s], acc, 0, 0, 0);
+            if (k > 1) {
+#pragma unroll
+                for (int s = 0; s < 8; ++s) bw[s] = frag(net.WT + (size_t)(k - 1) * kMlpWidth * kMlpWidth, kMlpWidth, col, s);
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) dH[j] = acc[j];
+        }
+        float bsum = 0.0f;                              // bias gradient, the slope product unrounded
+        if (par < 2) {
+#pragma unroll 8
+            for (int r = par; r < kTrainRows; r += 2) bsum = fmaf(Gs[r * kMlpWidth + kk], Ss[r * kMlpWidth + kk], bsum);
+            if (par == 1) odd[kk] = bsum;
+        }
+        __syncthreads();
+        if (par == 0) out[k * kMlpWidth + kk] = bsum + odd[kk];
+    }
+}
+
+// Weight gradients of the hidden layers: chain u of layer y (blockIdx) sums the
+// groups u, u + 4, .. (the last groups % 4 join chain 0), each group's product
+// from zero: part[layer][u][n][k].  A workgroup takes one 32 x 32 tile of a
+// chain; its eight wavefronts take eight groups at a time and the sums follow in
+// order from LDS.  Operands are 16-byte loads of transposed tiles.  Workgroups go
+// to the XCDs round-robin: the 16 tiles of a chain, which share its operands,
+// have one id modulo 8.
+__global__ __launch_bounds__(512) void k_mlp_wgrad(const __bf16 *HT, const __bf16 *DT, int rows, int chunk, int groups,
+                                                   float *part) {
+    __shared__ float P[8][32 * 32];
+    const int chain = (blockIdx.x & 7) + 8 * (blockIdx.x >> 7), tile = (blockIdx.x >> 3) & 15;
+    const int layer = chain >> 2, u = chain & 3, n0 = 32 * (tile >> 2), k0 = 32 * (tile & 3);
+    const int l = threadIdx.x & 63, w = threadIdx.x >> 6, half = l >> 5, lane = l & 31;
+    const int quads = groups >> 2;
+    const int len = quads + (u == 0 ? groups & 3 : 0);      // groups of this chain
+    float s[2] = {0.0f, 0.0f};                              // elements threadIdx.x and threadIdx.x + 512
+    auto load = [&](const __bf16 *T, int c0, int r0) {      // column c0 + lane, rows r0 + 8 half ..
+        const __bf16 *t = T + ((size_t)(r0 >> 6) * kMlpDepth + layer) * kTileT;
+        return *reinterpret_cast<const bf16x8 *>(t + (size_t)(c0 + lane) * kTrainRows + (r0 & 63) + 8 * half);
+    };
+    for (int j0 = 0; j0 < len; j0 += 8) {
+        const int j = j0 + w;
+        floatx16 acc = {};
+        if (j < len) {
+            const int g = j < quads ? 4 * j + u : 4 * quads + (j - quads);
+            const int r_end = min(rows, (g + 1) * chunk);
+            for (int r0 = g * chunk; r0 < r_end; r0 += 128) {
+                bf16x8 a[8], b[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int r = min(r0 + 16 * q, (r_end - 1) & ~15);   // (past the end: loaded, not used)
+                    a[q] = load(DT, n0, r);
+                    b[q] = load(HT, k0, r);
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (r0 + 16 * q < r_end) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[q], b[q], acc, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) P[w][((e / 4) * 8 + half * 4 + (e % 4)) * 32 + lane] = acc[e];
+        __syncthreads();
+        const int cnt = min(8, len - j0);
+        for (int q = 0; q < cnt; ++q) {
+            s[0] += P[q][threadIdx.x];
+            s[1] += P[q][threadIdx.x + 512];
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) loss_partial[blockIdx.x] = red[0] / npair;
-}
-
-// dH6 = dY Wo  (the output layer has K = 6: plain FP32; silu' is applied by k_mlp_dz)
-__global__ void k_mlp_out_back(const float *dY, const float *Wo_master, int rows, float *dH) {
-    const int k = threadIdx.x, row = blockIdx.x;
-    if (row >= rows) return;
-    float s = 0.0f;
+    float *out = part + ((size_t)layer * 4 + u) * kMlpWidth * kMlpWidth;
 #pragma unroll
-    for (int c = 0; c < kMlpOut; ++c) s += dY[(size_t)row * kMlpOut + c] * Wo_master[c * kMlpWidth + k];
-    dH[(size_t)row * kMlpWidth + k] = s;
-}
-
-// Row-parallel column work: a 256-thread block takes kColRows = 64 rows, thread
-// (half = tid / 128, k = tid % 128) the rows r0 + half + 2i of column k.
-
-// dZ = dH * silu'(Z) -> bf16, and per-block column sums (bias gradient)
-__global__ __launch_bounds__(256) void k_mlp_dz(const float *dH, const float *Z, int rows, __bf16 *dZ,
-                                                float *bias_partial) {
-    __shared__ float red[kMlpWidth];
-    const int k = threadIdx.x & (kMlpWidth - 1), half = threadIdx.x >> 7;
-    const int r0 = blockIdx.x * kColRows;
-    float s = 0.0f;
-    for (int i = half; i < kColRows; i += 2) {
-        const int r = r0 + i;
-        if (r >= rows) break;
-        const float v = dH[(size_t)r * kMlpWidth + k] * dsilu_f(Z[(size_t)r * kMlpWidth + k]);
-        dZ[(size_t)r * kMlpWidth + k] = (__bf16)v;
-        s += v;
+    for (int q = 0; q < 2; ++q) {
+        const int e = threadIdx.x + 512 * q;
+        out[(n0 + (e >> 5)) * kMlpWidth + k0 + (e & 31)] = s[q];
     }
-    if (half) red[k] = s;
-    __syncthreads();
-    if (!half) bias_partial[(size_t)blockIdx.x * kMlpWidth + k] = s + red[k];
 }
 
-// output layer: dWo[c][k] = sum_r dY[r][c] H6[r][k], dco[c] = sum_r dY[r][c]  (per-block partials)
-__global__ __launch_bounds__(256) void k_mlp_out_grad(const float *dY, const __bf16 *H6, int rows, float *partial) {
-    __shared__ float red[kMlpOut * kMlpWidth + kMlpOut];
-    const int k = threadIdx.x & (kMlpWidth - 1), half = threadIdx.x >> 7;
-    const int r0 = blockIdx.x * kColRows;
-    float s[kMlpOut] = {0, 0, 0, 0, 0, 0}, sb[kMlpOut] = {0, 0, 0, 0, 0, 0};
-    for (int i = half; i < kColRows; i += 2) {
-        const int r = r0 + i;
-        if (r >= rows) break;
-        const float h = (float)H6[(size_t)r * kMlpWidth + k];
-#pragma unroll
-        for (int c = 0; c < kMlpOut; ++c) {
-            const float d = dY[(size_t)r * kMlpOut + c];
-            s[c] += d * h;
-            sb[c] += d;
+// Slot of evaluation column k within its 32-block: the inverse of mlp_perm.
+__device__ __forceinline__ int mlp_perm_slot(int k) { return 8 * ((k >> 2) & 3) + 4 * (k >> 4) + (k & 3); }
+
+// One parameter's gradient g: stored, and with apply its Adam step taken on the
+// FP32 master.  Returns the parameter.
+__device__ __forceinline__ float adam_step(const TrainNet &net, const AdamArgs &a, int i, float g) {
+    net.g[i] = g;
+    float p = net.p[i];
+    if (a.apply) {
+        const float mi = a.b1 * net.mo[i] + (1.0f - a.b1) * g;
+        const float vi = a.b2 * net.ve[i] + (1.0f - a.b2) * g * g;
+        net.mo[i] = mi;
+        net.ve[i] = vi;
+        p -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+        net.p[i] = p;
+    }
+    return p;
+}
+
+// Blocks [0, kUpdateW): 256 hidden weights each, the four chains of their gradient;
+// then 64 of the other sums each, over the blocks of k_mlp_train, one thread a
+// chain; the last: the loss.  With apply the BF16 copies are rewritten too.
+constexpr int kUpdateW = kMlpDepth * kMlpWidth * kMlpWidth / 256;
+constexpr int kUpdateS = (kTrainSums + 63) / 64;
+
+__global__ __launch_bounds__(256) void k_mlp_update(TrainNet net, AdamArgs a, const float *part, const float *sums,
+                                                    const double *loss_part, int nblk, volatile double *loss_host) {
+    const int tid = threadIdx.x, blk = blockIdx.x;
+    if (blk < kUpdateW) {
+        constexpr int WW = kMlpWidth * kMlpWidth;
+        const int i = blk * 256 + tid, layer = i / WW, e = i % WW;
+        const float *P = part + (size_t)layer * 4 * WW + e;
+        const float p = adam_step(net, a, kMlpOffW + i, (P[0] + P[WW]) + (P[2 * WW] + P[3 * WW]));
+        if (a.apply) {
+            const int n = e / kMlpWidth, k = e % kMlpWidth;
+            const __bf16 v = (__bf16)p;
+            net.W[i] = v;
+            net.WT[(size_t)layer * WW + k * kMlpWidth + n] = v;
+            net.We[(size_t)layer * WW + n * kMlpWidth + (layer == 0 ? k : (k & ~31) + mlp_perm_slot(k & 31))] = v;
         }
+        return;
     }
-    if (half) {
+    if (blk < kUpdateW + kUpdateS) {
+        __shared__ float red[4][64];
+        const int o = (blk - kUpdateW) * 64 + (tid & 63), u = tid >> 6;
+        float s = 0.0f;
+        if (o < kTrainSums) {
+            const float *S = sums + o;
+            const int quads = nblk >> 2;
+            int q = 0;
+            for (; q + 16 <= quads; q += 16) {          // sixteen loads in flight, added in order
+                float v[16];
 #pragma unroll
-        for (int c = 0; c < kMlpOut; ++c) red[c * kMlpWidth + k] = s[c];
-        if (k < kMlpOut) red[kMlpOut * kMlpWidth + k] = sb[k];
+                for (int x = 0; x < 16; ++x) v[x] = S[(size_t)(4 * (q + x) + u) * kTrainSums];
+#pragma unroll
+                for (int x = 0; x < 16; ++x) s += v[x];
+            }
+            for (; q < quads; ++q) s += S[(size_t)(4 * q + u) * kTrainSums];
+            if (u == 0)
+                for (int g = 4 * quads; g < nblk; ++g) s += S[(size_t)g * kTrainSums];
+        }
+        red[u][tid & 63] = s;
+        __syncthreads();
+        if (u != 0 || o >= kTrainSums) return;
+        const float g = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+        constexpr int nc = kMlpDepth * kMlpWidth, nw = kMlpOut * kMlpWidth;
+        const int i = o < nc ? kMlpOffC + o : o < nc + nw ? kMlpOffWo + (o - nc) : kMlpOffCo + (o - nc - nw);
+        const float p = adam_step(net, a, i, g);
+        if (a.apply && o >= nc && o < nc + nw) {
+            const int e = o - nc, n = e / kMlpWidth, k = e % kMlpWidth;
+            net.Wo[e] = (__bf16)p;
+            net.Woe[n * kMlpWidth + (k & ~31) + mlp_perm_slot(k & 31)] = (__bf16)p;
+        }
+        return;
     }
+    __shared__ double sum[256];
+    double v = 0.0;
+    for (int g = tid; g < nblk; g += 256) v += loss_part[g];
+    sum[tid] = v;
     __syncthreads();
-    if (!half) {
-        float *P = partial + (size_t)blockIdx.x * (kMlpOut * kMlpWidth + kMlpOut);
-#pragma unroll
-        for (int c = 0; c < kMlpOut; ++c) P[c * kMlpWidth + k] = s[c] + red[c * kMlpWidth + k];
-        if (k < kMlpOut) P[kMlpOut * kMlpWidth + k] = sb[k] + red[kMlpOut * kMlpWidth + k];
+    for (int s = 128; s > 0; s >>= 1) {
+        if (tid < s) sum[tid] += sum[tid + s];
+        __syncthreads();
     }
-}
-
-// ---------------------------------------------------------------------------
-// Adam on the fp32 master parameters, then the bf16 copies used by the MFMA
-// products (W row-major, W transposed, Wo).
-// ---------------------------------------------------------------------------
-__global__ void k_adam(float *p, float *mo, float *ve, const float *g, int n, float lr, float b1, float b2, float eps,
-                       float c1, float c2) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * mo[i] + (1.0f - b1) * gi;
-    const float vi = b2 * ve[i] + (1.0f - b2) * gi * gi;
-    mo[i] = mi;
-    ve[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    if (tid == 0) *loss_host = sum[0];
 }
 
 // W, WT, Wo: natural order (training products); We, Woe: evaluation order
@@ -297,82 +445,18 @@ __global__ void k_field_sample(FieldDev f, const double *pts, int n, double *out
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t mlp_launch_features(const MlpArgs &m, const double *pts, int n, __bf16 *H0, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_features, dim3((n + 3) / 4), dim3(64, 4), 0, s, m, pts, n, H0);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_forward_layer(const __bf16 *A, const __bf16 *W, const float *bias, int rows, float *Z,
-                                    __bf16 *H, hipStream_t s) {
-    hipLaunchKernelGGL((k_mlp_gemm<0, 4>), dim3((rows + 127) / 128), dim3(256), 0, s, A, W, bias, rows, Z, H);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_output(const __bf16 *A, const __bf16 *Wo, const float *co, int rows, float *Y, hipStream_t s) {
-    hipLaunchKernelGGL((k_mlp_gemm<2, 1>), dim3((rows + 127) / 128), dim3(256), 0, s, A, Wo, co, rows, Y,
-                       (__bf16 *)nullptr);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_backward_data(const __bf16 *dZ, const __bf16 *WT, int rows, float *dH, hipStream_t s) {
-    hipLaunchKernelGGL((k_mlp_gemm<1, 4>), dim3((rows + 127) / 128), dim3(256), 0, s, dZ, WT, (const float *)nullptr,
-                       rows, dH, (__bf16 *)nullptr);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_wgrad(const __bf16 *D, const __bf16 *H, int rows, int groups, float *partial, float *out,
+hipError_t mlp_launch_train(const MlpArgs &m, const TrainNet &net, const double *pts, const double *tgt, int npair,
+                            const MlpLoss &L, const AdamArgs &adam, const TrainBufs &w, volatile double *loss_host,
                             hipStream_t s) {
-    const int chunk = ((rows + groups - 1) / groups + 15) / 16 * 16;
-    const int g = (rows + chunk - 1) / chunk;
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3(g), dim3(256), 0, s, D, H, rows, chunk, partial);
-    const int count = kMlpWidth * kMlpWidth;
-    hipLaunchKernelGGL(k_sum_partials, dim3((count + 255) / 256), dim3(256), 0, s, partial, g, count, out, 0);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_loss(const MlpArgs &m, const double *pts, const double *tgt, const float *Y, int npair,
-                           const MlpLoss &L, float *dY, double *loss_partial, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_loss, dim3(blocks), dim3(256), 0, s, m, pts, tgt, Y, npair, L, dY, loss_partial);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_out_back(const float *dY, const float *Wo_master, int rows, float *dH, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_out_back, dim3(rows), dim3(kMlpWidth), 0, s, dY, Wo_master, rows, dH);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_dz(const float *dH, const float *Z, int rows, __bf16 *dZ, float *bias_partial,
-                         float *bias_out, hipStream_t s) {
-    const int g = (rows + kColRows - 1) / kColRows;
-    hipLaunchKernelGGL(k_mlp_dz, dim3(g), dim3(256), 0, s, dH, Z, rows, dZ, bias_partial);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kMlpWidth), 0, s, bias_partial, g, kMlpWidth, bias_out, 0);
-    return hipGetLastError();
-}
-
-hipError_t mlp_launch_out_grad(const float *dY, const __bf16 *H6, int rows, float *partial, float *dWo, float *dco,
-                               hipStream_t s) {
-    const int g = (rows + kColRows - 1) / kColRows;
-    hipLaunchKernelGGL(k_mlp_out_grad, dim3(g), dim3(256), 0, s, dY, H6, rows, partial);
-    const int count = kMlpOut * kMlpWidth + kMlpOut;
-    // the partial block is [c][k] then [c]: sum into a staging area laid out the same way
-    hipLaunchKernelGGL(k_sum_partials, dim3((count + 255) / 256), dim3(256), 0, s, partial, g, count,
-                       partial + (size_t)g * count, 0);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(dWo, partial + (size_t)g * count, kMlpOut * kMlpWidth * sizeof(float),
-                           hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(dco, partial + (size_t)g * count + kMlpOut * kMlpWidth, kMlpOut * sizeof(float),
-                           hipMemcpyDeviceToDevice, s);
-    return e;
-}
-
-
-hipError_t mlp_launch_adam(float *p, float *mo, float *ve, const float *g, int n, float lr, float b1, float b2,
-                           float eps, int step, hipStream_t s) {
-    const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
-    hipLaunchKernelGGL(k_adam, dim3((n + 255) / 256), dim3(256), 0, s, p, mo, ve, g, n, lr, b1, b2, eps, c1, c2);
+    const int rows = 2 * npair, nblk = mlp_train_blocks(npair);
+    const int chunk = mlp_train_chunk(rows), groups = (rows + chunk - 1) / chunk;
+    hipLaunchKernelGGL(k_mlp_train<false>, dim3(nblk), dim3(kTrainThreads), 0, s, m, net, pts, tgt, npair, L, w.Y, w.HT,
+                       w.DT, w.sums, w.loss);
+    hipLaunchKernelGGL(k_mlp_train<true>, dim3(nblk), dim3(kTrainThreads), 0, s, m, net, pts, tgt, npair, L, w.Y, w.HT,
+                       w.DT, w.sums, w.loss);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(16 * 4 * kMlpDepth), dim3(512), 0, s, w.HT, w.DT, rows, chunk, groups, w.part);
+    hipLaunchKernelGGL(k_mlp_update, dim3(kUpdateW + kUpdateS + 1), dim3(256), 0, s, net, adam, w.part, w.sums, w.loss,
+                       nblk, loss_host);
     return hipGetLastError();
 }
 

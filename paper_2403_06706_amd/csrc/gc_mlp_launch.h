@@ -12,25 +12,40 @@ struct MlpLoss {
     double beta;          // weight of the paired-difference term
 };
 
-hipError_t mlp_launch_features(const MlpArgs &m, const double *pts, int n, __bf16 *H0, hipStream_t s);
-hipError_t mlp_launch_forward_layer(const __bf16 *A, const __bf16 *W, const float *bias, int rows, float *Z,
-                                    __bf16 *H, hipStream_t s);
-hipError_t mlp_launch_output(const __bf16 *A, const __bf16 *Wo, const float *co, int rows, float *Y, hipStream_t s);
-hipError_t mlp_launch_backward_data(const __bf16 *dZ, const __bf16 *WT, int rows, float *dH, hipStream_t s);
-hipError_t mlp_launch_wgrad(const __bf16 *D, const __bf16 *H, int rows, int groups, float *partial, float *out,
+// Parameters of the network on the device: FP32 masters p with their gradient
+// and Adam moments, c, co and Wo_master within p, and the BF16 copies.
+struct TrainNet {
+    float *p, *mo, *ve, *g;
+    const float *c, *co, *Wo_master;
+    __bf16 *W, *WT, *Wo, *We, *Woe;
+};
+struct AdamArgs {
+    float lr, b1, b2, eps, c1, c2;   // c1 = 1 - b1^step, c2 = 1 - b2^step
+    int apply;                       // 0: gradient only
+};
+// Workspace of a training step
+struct TrainBufs {
+    float *Y;             // outputs [rows][6]
+    __bf16 *HT, *DT;      // transposed tiles of H_0..H_5 and of dZ_1..dZ_6
+    float *part;          // weight-gradient chains [6][4][128][128]
+    float *sums;          // per block: bias gradients, dWo, dco
+    double *loss;         // per block
+};
+constexpr int kTrainRows = 64;                                      // of a block
+constexpr int kTrainSums = kMlpDepth * kMlpWidth + kMlpOut * kMlpWidth + kMlpOut;
+__host__ __device__ constexpr int mlp_train_blocks(int64_t npair) {
+    return (int)((2 * npair + kTrainRows - 1) / kTrainRows);
+}
+// Rows of a weight-gradient group: about 128 groups, of whole 16-row products and
+// at least 128 rows.
+__host__ __device__ constexpr int mlp_train_chunk(int rows) {
+    const int g = rows / 128 < 1 ? 1 : rows / 128 > 128 ? 128 : rows / 128;
+    return ((rows + g - 1) / g + 15) / 16 * 16;
+}
+// One training step.  *loss_host (coherent host memory) receives the loss.
+hipError_t mlp_launch_train(const MlpArgs &m, const TrainNet &net, const double *pts, const double *tgt, int npair,
+                            const MlpLoss &L, const AdamArgs &adam, const TrainBufs &w, volatile double *loss_host,
                             hipStream_t s);
-hipError_t mlp_launch_loss(const MlpArgs &m, const double *pts, const double *tgt, const float *Y, int npair,
-                           const MlpLoss &L, float *dY, double *loss_partial, int blocks, hipStream_t s);
-hipError_t mlp_launch_out_back(const float *dY, const float *Wo_master, int rows, float *dH, hipStream_t s);
-hipError_t mlp_launch_dz(const float *dH, const float *Z, int rows, __bf16 *dZ, float *bias_partial,
-                         float *bias_out, hipStream_t s);
-hipError_t mlp_launch_out_grad(const float *dY, const __bf16 *H6, int rows, float *partial, float *dWo, float *dco,
-                               hipStream_t s);
-constexpr int kColRows = 64;     // rows per block of the row-parallel column sums
-// partial blocks of the row-parallel column sums
-__host__ __device__ constexpr int mlp_col_groups(int rows) { return (rows + kColRows - 1) / kColRows; }
-hipError_t mlp_launch_adam(float *p, float *mo, float *ve, const float *g, int n, float lr, float b1, float b2,
-                           float eps, int step, hipStream_t s);
 hipError_t mlp_launch_refresh(const float *p, __bf16 *W, __bf16 *WT, __bf16 *Wo, __bf16 *We, __bf16 *Woe,
                               hipStream_t s);
 hipError_t mlp_launch_eval(const MlpArgs &m, const double *pts, int n, double *out, hipStream_t s);
