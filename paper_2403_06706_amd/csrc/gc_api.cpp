@@ -297,14 +297,11 @@ uint32_t bits_for(uint32_t max_key) {
 // earlier reorder is below tail_threshold, the machine is far from full and the
 // push is bound by each wavefront's chain of dependent memory round trips.
 // Then the push takes a latency form (below quad_limit four lanes per
-// particle; the full equations all loads of a gather in flight), and the
-// reorder runs only every kTailReorderEvery chunks (particles cross about two
+// particle, else all loads of a gather in flight), and the reorder runs only
+// every kTailReorderEvery chunks (particles cross about two
 // cells per 64 steps, so the cell order decays slowly, while a reorder costs a
-// fixed ~70 us of launches).  The full equations load two whole stencils per
-// evaluation and feel the decay more: every 4 chunks (90,001 electrons, 1,024
-// steps: 13.0 ms every 8, 12.4 every 4, 11.9 every 2; 5,000: 6.30, 6.26, 6.31).
-// No choice changes any particle's trajectory.
-constexpr int kTailReorderEvery = 8, kTailReorderEveryFull = 4;
+// fixed ~70 us of launches).  No choice changes any particle's trajectory.
+constexpr int kTailReorderEvery = 8;
 // The live count read back is only as fresh as the host's lead over the
 // device: with the tail policy on, the host issues a chunk only once the chunk
 // issued kAhead chunks earlier has finished (enough queued work to hide the
@@ -337,7 +334,7 @@ int push_form(const gc_ctx *ctx) {
     const uint32_t n = live_bound(ctx), T = (uint32_t)ctx->opt.tail_threshold;
     if (n >= T) return 0;
     const bool f64 = ctx->opt.precision == GC_PREC_F64, full = ctx->fx.data != nullptr;
-    return n < quad_limit(T, f64, ctx->f.dtype, full, false) ? 2 : 1;
+    return n < quad_limit(T, f64, ctx->f.dtype, full) ? 2 : 1;
 }
 
 gc_status finish_reorder(gc_ctx *ctx, int order, hipEvent_t e0, hipEvent_t e1, hipEvent_t p0, hipEvent_t p1);
@@ -489,7 +486,7 @@ gc_status enqueue_advance(gc_ctx *ctx, double dt, int64_t n_steps, bool timed) {
         gc_status st = GC_OK;
         if (!tail || ctx->bound_dirty || ctx->tail_skip <= 0) {
             st = reorder(ctx, timed && ctx->opt.timing == 1, ctx->opt.order);   // (timing 2: pushes only)
-            ctx->tail_skip = (ctx->fx.data ? kTailReorderEveryFull : kTailReorderEvery) - 1;
+            ctx->tail_skip = kTailReorderEvery - 1;
         } else {
             --ctx->tail_skip;
         }

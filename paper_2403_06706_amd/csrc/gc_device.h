@@ -177,21 +177,20 @@ __device__ __forceinline__ void gather_add(const FieldDev &f, const GatherPlan<R
     for (int c = 0; c < 12; ++c) out[c] = fma(wb, (R)p.get(c + 12, f), fma(wa, (R)p.get(c, f), out[c]));
 }
 
-template <typename R>
-__device__ __forceinline__ bool finite12(const R out[12]) {
+template <int N, typename R>
+__device__ __forceinline__ bool finite_sum(const R out[N]) {
     R sum = (R)0;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) sum += out[c];
+    for (int c = 0; c < N; ++c) sum += out[c];
     return isfinite(sum);
 }
+template <typename R>
+__device__ __forceinline__ bool finite12(const R out[12]) { return finite_sum<12>(out); }
 
-// One lane: the four node pairs added in order.
-// kAllPairs: issue the loads of all four node pairs at once (one memory round
-// trip per gather, more registers); otherwise at most two pairs are in
-// registers at a time, which keeps the push within two wavefronts per SIMD.
-// The arithmetic, and so the result, is the same either way.  kTame: the
-// caller knows the field is tame (FieldDev::tame): no finiteness test.
-template <int FDT, typename R, bool kAllPairs = false, bool kTame = false>
+// One lane: the four node pairs added in order, at most two of them in registers
+// at a time.  kTame: the caller knows the field is tame (FieldDev::tame): no
+// finiteness test.
+template <int FDT, typename R, bool kTame = false>
 __device__ __forceinline__ bool gather(const FieldDev &f, R r, R th, R ph, R out[12]) {
     GatherPlan<R> gp;
     if (!gather_plan<FDT>(f, r, th, ph, gp)) return false;
@@ -202,7 +201,7 @@ __device__ __forceinline__ bool gather(const FieldDev &f, R r, R th, R ph, R out
         Pair<FDT> p;
         p.load(f.data, gp.off[q], gp.dk, gp.cs);
         gather_add<FDT, R>(f, gp, q, p, out);
-        if (!kAllPairs && (q & 1)) __builtin_amdgcn_sched_barrier(0);   // at most two node pairs in registers
+        if (q & 1) __builtin_amdgcn_sched_barrier(0);   // at most two node pairs in registers
     }
     if constexpr (kTame) return true;
     else return finite12(out);
@@ -242,29 +241,45 @@ __device__ __forceinline__ bool in_unit(float a, float b, float c) {
 template <typename T>
 __device__ __forceinline__ void forget(T &x) { asm volatile("" : "=v"(x)); }
 
-// The nodes of a cell, one lane per particle (FP32 and FP16 fields): chunk c of
-// node h of pair p at q[(2 p + h) 3 + c].
-template <int FDT>
+// The nodes of a cell, one lane per particle: chunk c of node h of pair p at
+// q[(2 p + h) kWhole + c].  NC = 9: the extra array of the full equations (9
+// components and 3 zeros a node), the ninth alone in last (FP16: whole chunks).
+template <int FDT, int NC = 12>
 struct LaneCell {
-    using V = typename std::conditional<FDT == GC_F32, float __attribute__((ext_vector_type(4))),
-                                        uint32_t __attribute__((ext_vector_type(2)))>::type;
-    V q[24];
+    static constexpr int W = Layout<FDT>::W, kChunks = Layout<FDT>::nch;
+    static constexpr int kWhole = FDT == GC_F16 ? kChunks : NC / W;          // chunks loaded whole
+    static constexpr bool kLast = kWhole * W < NC;
+    using T = typename std::conditional<FDT == GC_F64, double, float>::type;
+    using V = typename std::conditional<FDT == GC_F64, double __attribute__((ext_vector_type(2))),
+              typename std::conditional<FDT == GC_F32, float __attribute__((ext_vector_type(4))),
+                                        uint32_t __attribute__((ext_vector_type(2)))>::type>::type;
+    V q[8 * kWhole];
+    T last[kLast ? 8 : 1];
     template <typename R>
     __device__ __forceinline__ void load(const FieldDev &f, const GatherPlan<R> &gp, uint32_t) {
-        constexpr uint32_t E = sizeof(V) / 4;             // bytes of a component
+        constexpr uint32_t E = sizeof(V) / W;             // bytes of a component
         const char *b = static_cast<const char *>(f.data);
 #pragma unroll
-        for (int i = 0; i < 24; ++i)
-            q[i] = *reinterpret_cast<const V *>(b + (size_t)((i % 3) * gp.cs) * E + (gp.off[i / 6] + ((i / 3) & 1) * gp.dk) * E);
+        for (int n = 0; n < 8; ++n)
+#pragma unroll
+            for (int c = 0; c < kWhole + (kLast ? 1 : 0); ++c) {
+                const char *a = b + (size_t)(c * gp.cs) * E + (gp.off[n / 2] + (n & 1) * gp.dk) * E;
+                if (c < kWhole) q[n * kWhole + c] = *reinterpret_cast<const V *>(a);
+                else last[n] = *reinterpret_cast<const T *>(a);
+            }
     }
-    __device__ __forceinline__ float get(int p, int h, int c, const FieldDev &f) const {
-        const V v = q[(2 * p + h) * 3 + c / 4];
-        if constexpr (FDT == GC_F32) return v[c % 4];
+    __device__ __forceinline__ T get(int p, int h, int c, const FieldDev &f) const {
+        if (kLast && c == NC - 1) return last[2 * p + h];
+        const V v = q[(2 * p + h) * kWhole + c / W];
+        if constexpr (FDT != GC_F16) return v[c % W];
         else return __half2float(__ushort_as_half((unsigned short)(v[(c % 4) / 2] >> (16 * (c % 2))))) * f.scale[c];
     }
     __device__ __forceinline__ void drop() {
 #pragma unroll
-        for (int i = 0; i < 24; ++i) forget(q[i]);
+        for (int i = 0; i < 8 * kWhole; ++i) forget(q[i]);
+        if (kLast)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) forget(last[i]);
     }
     // components [c0, c1) at the weights of at
     template <int c0, int c1, typename R>
@@ -353,8 +368,13 @@ struct QuadCell {
     }
 };
 
-template <int FDT, typename R, typename Cell>
-__device__ __forceinline__ bool cell_seek(const FieldDev &f, R r, R th, R ph, uint32_t gl, CellPos<R> &at, Cell &cell) {
+// more: null, or the extra array's cell (description fx) moved along with it.
+struct NoCell {
+    template <typename R> __device__ __forceinline__ void load(const FieldDev &, const GatherPlan<R> &, uint32_t) {}
+};
+template <int FDT, typename R, typename Cell, typename More = NoCell>
+__device__ __forceinline__ bool cell_seek(const FieldDev &f, R r, R th, R ph, uint32_t gl, CellPos<R> &at, Cell &cell,
+                                          const FieldDev &fx, More &more) {
     const R x = (r - (R)f.r_min) * (R)f.inv_dr;
     const R y = th * (R)f.inv_dth - (R)0.5;
     const R z = ph * (R)f.inv_dph;
@@ -373,38 +393,9 @@ __device__ __forceinline__ bool cell_seek(const FieldDev &f, R r, R th, R ph, ui
         at.wt = clampr(y - at.fj, (R)0, (R)1);
         at.wp = z - at.zf;
         cell.load(f, gp, gl);
+        more.load(fx, gp, gl);
     }
     return true;
-}
-
-// The field and the extra node array of the full Eqs. 1-2 (same geometry and
-// layout, fx the extra array's description) at one point, with one stencil:
-// the same operations and order as gather() on each array.  Returns what
-// gather() returns for the field; xok what it returns for the extra array.
-template <int FDT, typename R, bool kAllPairs = false>
-__device__ __forceinline__ bool gather2(const FieldDev &f, const FieldDev &fx, R r, R th, R ph, R out[12],
-                                        R xout[12], bool &xok) {
-    GatherPlan<R> gp;
-    xok = false;
-    if (!gather_plan<FDT>(f, r, th, ph, gp)) return false;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) out[c] = xout[c] = (R)0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        Pair<FDT> p;
-        p.load(f.data, gp.off[q], gp.dk, gp.cs);
-        gather_add<FDT, R>(f, gp, q, p, out);
-        if (!kAllPairs && (q & 1)) __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        Pair<FDT> p;
-        p.load(fx.data, gp.off[q], gp.dk, gp.cs);
-        gather_add<FDT, R>(fx, gp, q, p, xout);
-        if (!kAllPairs && (q & 1)) __builtin_amdgcn_sched_barrier(0);
-    }
-    xok = finite12(xout);
-    return finite12(out);
 }
 
 // ---------------------------------------------------------------------------

@@ -9,26 +9,22 @@ namespace gc {
 
 constexpr int kMaxEnsembles = 4096;
 // Tail policy: fewer live particles than this (a share of the tail threshold T)
-// take the four-lanes-per-particle form; from there to T, one lane per particle.
+// take the four-lanes-per-particle form; from there on, one lane per particle.
 // The line lies where the quad form's wavefronts begin to share a SIMD (1,024 of
-// 16 particles, T/8 of the default 131,072), measured per 1,024 steps:
-//  * FP64 arithmetic on FP32 fields: 12,000 particles 2.26 ms (quad) against 2.82
-//    (lane), 20,011 3.03 against 2.90;
-//  * FP32 arithmetic on FP32 fields, whose shorter step gains from two quad
-//    wavefronts per SIMD: T/4 (30,000: 2.33 against 2.41; 50,000 the lane form);
-//  * FP64 fields: T, because the lane form cannot keep a cell of them and feels
-//    the order decay between the tail's rare reorders (50,000: 4.7 against 8.9 ms,
-//    128,000: 9.1 against 18.8; 250,000: 8.5 against 8.2 per 512).  Reordered every
-//    chunk (the persistent form) the two are as fast (50,000: 5.0 against 5.3,
-//    128,000: 10.0 against 9.2): T/4;
-//  * FP16 fields: never, the lane form keeps a cell in 48 registers and the quad
-//    form shared whole node pairs (12,000: 3.94 against 3.51);
+// 16 particles, T/8 of the default 131,072) or a little beyond, measured per 1,024
+// steps:
+//  * FP64 arithmetic on FP32 fields: T/8 (12,000 particles 2.26 ms in the quad form
+//    against 2.82, 20,011 3.03 against 2.90);
+//  * FP32 arithmetic, whose shorter step gains from two quad wavefronts per SIMD:
+//    T/4 (30,000 on an FP32 field 2.33 against 2.41, 50,000 the lane form);
+//  * FP64 fields, whose lane form has one wavefront per SIMD: T/4 (30,000: 2.99
+//    against 3.07 ms, 50,000: 4.65 against 3.15);
+//  * FP16 fields: never, the lane form keeps a cell in 48 registers (12,000: 3.51
+//    against 3.94 in a quad form that shared whole node pairs);
 //  * the full equations have no quad form.
-__host__ __device__ constexpr uint32_t quad_limit(uint32_t T, bool f64_arithmetic, int field_dtype, bool full,
-                                                  bool every_chunk) {
+__host__ __device__ constexpr uint32_t quad_limit(uint32_t T, bool f64_arithmetic, int field_dtype, bool full) {
     if (full || field_dtype == GC_F16) return 0;
-    if (field_dtype == GC_F64) return every_chunk ? T / 4 : T;
-    return f64_arithmetic ? T / 8 : T / 4;
+    return f64_arithmetic && field_dtype == GC_F32 ? T / 8 : T / 4;
 }
 constexpr int kMaxMoments = 8192;
 constexpr int64_t kMaxRebirthSteps = 1 << 24;   // generations fit the 24 flag bits above GC_FLAG_GEN_SHIFT

@@ -33,8 +33,8 @@ inline void launch_timed(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStr
         hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
 }
 
-// push (gc_push.hip); form: 0 throughput, 1 all pairs of a gather in flight,
-// 2 four lanes per particle (the last two for few active particles)
+// push (gc_push.hip); form: 0 one lane per particle, 1 the same in the tail,
+// 2 four lanes per particle (for few active particles)
 hipError_t launch_push(const PushArgs &a, int precision, int block, bool persistent, int form, int grid_blocks,
                        hipStream_t s, LaunchEvents ev = {});
 

@@ -13,20 +13,16 @@
 
 namespace gc {
 
-// Forms of the push (all bitwise identical in their results):
-//   kFormLane      one lane per particle, at most 256 registers (two wavefronts per SIMD).
-//                  FP32 and FP16 fields: resident cells, every load of a gather in flight at
-//                  once.  FP64 fields and the full equations: every stencil loaded, two node
-//                  pairs of a gather in registers at a time;
-//   kFormAllPairs  FP64 fields and the full equations in the tail (kHasAllPairs): the same
-//                  with all four pairs of a gather in flight;
-//   kFormQuad      four lanes per particle (an aligned quad), FP32 and FP64 fields: each lane
-//                  keeps and interpolates three of the twelve components, the quad shares the
-//                  results, all four run the rest of the step on identical values, lane
-//                  gl = 0 writes.
-enum { kFormLane = 0, kFormAllPairs = 1, kFormQuad = 2 };
+// Forms of the push (bitwise identical in their results):
+//   kFormLane   one lane per particle; a cell's nodes stay in its registers, so the loads of
+//               a gather are made on a change of cell only, all in flight at once;
+//   kFormTail   the same, below the tail threshold (the steps are counted apart);
+//   kFormQuad   four lanes per particle (an aligned quad), FP32 and FP64 fields: each lane
+//               keeps and interpolates three of the twelve components, the quad shares the
+//               results, all four run the rest of the step on identical values, lane gl = 0
+//               writes.
+enum { kFormLane = 0, kFormTail = 1, kFormQuad = 2 };
 template <int FDT, int MODE> constexpr bool kHasQuad = MODE != 2 && FDT != GC_F16;
-template <int FDT, int MODE> constexpr bool kHasAllPairs = MODE == 2 || FDT == GC_F64;
 
 // MODE 0: the reduced equations, no rebirth, centres at rest.  MODE 1: also
 // rebirth and scattering in the wind frame (Sect. 3 and 3.3); a separate
@@ -95,45 +91,33 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
     // Step ratio of the first step; every later one follows a step of size h (or
     // a bootstrap, whose ratio is 1).
     R tau = (R)dtp0 == h ? (R)1 : h * rcp_nr((R)dtp0);
-    // The gathers are cell-resident with one lane per particle on FP32 and FP16
-    // fields (96 registers of nodes), and in the quad form on FP32 and FP64 fields
-    // (24 or 48).  The others load every stencil: eight FP64 nodes (192), or the
-    // nodes of both arrays of the full equations, are more than the registers hold.
-    // Bound before: vector issue 0.70 and the gather paths (TA/TD) 0.68/0.73 busy,
-    // both evaluations of a step loading 24 x 16 bytes a lane.  An electron crosses
-    // a cell in about ten steps, so now some lanes of a wavefront load at X*, and
-    // seldom any at X^n.  Per 64-step launch (FP64 on an FP32 256x128x256 field):
-    // 2^20 electrons 2.40 -> 1.91 ms, 1,000 reborn electrons in the quad form
-    // 2.09 -> 1.71 us a step; 300,007 in FP32 arithmetic 0.61 -> 0.39 ms.
-    constexpr bool kResident = !FULL && (FORM == kFormQuad || FDT != GC_F64);
+    // Resident cells: 96 registers of nodes per lane for FP32 fields, 48 FP16, 192
+    // FP64, and 168, 96 and 336 with the extra array of the full equations; a quarter
+    // in the quad form (24 or 48).
+    // Bound when every gather loaded its stencil: vector issue 0.70 and the gather
+    // paths (TA/TD) 0.68/0.73 busy, both evaluations of a step loading 24 x 16 bytes a
+    // lane (FP64 fields 48).  An electron crosses a cell in about ten steps, so now some
+    // lanes of a wavefront load at X*, and seldom any at X^n.  Per 64-step launch (FP64
+    // on an FP32 256x128x256 field): 2^20 electrons 2.40 -> 1.91 ms, 1,000 reborn
+    // electrons in the quad form 2.09 -> 1.71 us a step; 300,007 in FP32 arithmetic 0.61
+    // -> 0.39 ms; full equations, 150,000: 0.88 -> 0.72 ms.
     using Cell = typename std::conditional<FORM == kFormQuad, QuadCell<FDT>, LaneCell<FDT>>::type;
     CellPos<R> at;
-    [[maybe_unused]] Cell cell;
-    constexpr std::integral_constant<int, 0> first;
-    constexpr std::integral_constant<int, 3> three;
-    constexpr std::integral_constant<int, 12> twelve;
-    // move to a point; then its components [c0, c1) into g (xg: the extra node
-    // array); both false where the point cannot be evaluated
-    auto seek = [&](R x, R t, R p) -> bool {
-        if constexpr (kResident) return cell_seek<FDT, R>(a.f, x, t, p, gl, at, cell);
-        else return true;
+    Cell cell;
+    [[maybe_unused]] typename std::conditional<FULL, LaneCell<FDT, 9>, NoCell>::type xcell;
+    // move to a point; false where it cannot be evaluated
+    auto seek = [&](R x, R t, R p) -> bool { return cell_seek<FDT, R>(a.f, x, t, p, gl, at, cell, a.fx, xcell); };
+    // the components there (and those of the extra array); false for a non-finite one
+    auto value = [&](R g[12]) -> bool {
+        cell.template value<0, 12, R>(a.f, at, gl, g);
+        return TAME || finite_sum<12>(g);
     };
-    auto value = [&](auto c0, auto c1, R x, R t, R p, R g[12], R xg[12], bool &xbad) -> bool {
-        xbad = false;
-        if constexpr (kResident) {
-            if constexpr (TAME) cell.template value<c0(), c1(), R>(a.f, at, gl, g);
-            else {
-                cell.template value<0, 12, R>(a.f, at, gl, g);
-                return finite12(g);
-            }
-            return true;
-        } else if constexpr (FULL) {
-            bool xok;
-            const bool ok = gather2<FDT, R, FORM == kFormAllPairs>(a.f, a.fx, x, t, p, g, xg, xok);
-            xbad = !xok;
-            return ok;
+    auto xvalue = [&](R xg[12]) -> bool {
+        if constexpr (FULL) {
+            xcell.template value<0, 9, R>(a.fx, at, gl, xg);
+            return finite_sum<9>(xg);
         }
-        else return gather<FDT, R, FORM == kFormAllPairs, TAME>(a.f, x, t, p, g);
+        return true;
     };
 
     // A bootstrap step needs a third evaluation, F^{n-1} at X^n - dt F^n.  A lane
@@ -167,9 +151,9 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
             // collision k+1 (Eqs. 9-10) at X^n: |p| kept, new pitch cosine and free path
             const CollisionDraw d = draw_collision(sr.id[ls], k + 1, flags >> GC_FLAG_GEN_SHIFT, e.seed, e.ensemble,
                                                    e.scatter_law, e.lambda);
-            R g[12], xg[12];
-            bool xbad;
-            if (!bad) bad = !value(first, three, px, pth, pph, g, xg, xbad);
+            R g[12];
+            if constexpr (TAME) cell.template value<0, 3, R>(a.f, at, gl, g);   // B alone
+            else if (!bad) bad = !value(g);
             if (!bad) {
                 const R mun = (R)d.mun;
                 const R B = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
@@ -192,9 +176,8 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
         {   // X^n (or X^{n-1} of a bootstrap)
             const R ir = rcp_nr(px), is = rcp_nr(sin_0_pi(pth));
             R g[12], xg[12];
-            bool xbad;
-            bad |= !value(first, twelve, px, pth, pph, g, xg, xbad);
-            if (FULL) bad |= xbad;
+            bad |= !xvalue(xg);
+            bad |= !value(g);
             rhs_at(ir, is, pu, g, xg, Fn, vpn);
         }
         bool go = true;
@@ -228,9 +211,8 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
                 R ir = rcp_nr(px), is = rcp_nr(sin_0_pi(pth));
                 asm volatile("" : "+v"(ir), "+v"(is));
                 R g[12], xg[12];
-                bool xbad;
-                bad |= !value(first, twelve, px, pth, pph, g, xg, xbad);
-                if (FULL) bad |= xbad;
+                bad |= !xvalue(xg);
+                bad |= !value(g);
                 rhs_at(ir, is, pu, g, xg, Fs, vps);
             }
             if (rare(bad)) {
@@ -274,10 +256,9 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
                         // from the injection state with its own generator stream
                         const uint32_t gen = (flags >> GC_FLAG_GEN_SHIFT) + 1;
                         const BirthState b = rebirth_state<FDT>(a.fdev, a.ens + eidx, sr.id[ls], gen);
-                        if constexpr (kResident) {   // another cell: its nodes need not be kept over the call
-                            at = CellPos<R>();
-                            cell.drop();
-                        }
+                        at = CellPos<R>();           // another cell: the nodes need not be kept over the call
+                        cell.drop();
+                        if constexpr (FULL) xcell.drop();
                         X0 = (A)b.r; X1 = (A)b.th; X2 = (A)b.ph; X3 = (A)b.u;
                         c0 = 0; c1 = 0; c2 = 0; c3 = 0; cT = 0; T = 0;
                         fp0 = 0; fp1 = 0; fp2 = 0; fp3 = 0;
@@ -345,23 +326,19 @@ __device__ __forceinline__ void push_grid(const PushArgs &a) {
     count_steps(a, taken);
 }
 
-// One lane per particle: at most 256 registers (two wavefronts per SIMD).
+// One lane per particle: at most 256 registers (two wavefronts per SIMD); the
+// larger cells of FP64 fields and of the full equations take the 512 of one.
+template <int FDT, int MODE> constexpr int kLaneWaves = MODE == 2 || FDT == GC_F64 ? 1 : 2;
+
 template <int PREC, int FDT, int MODE, bool TAME>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_push(PushArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kLaneWaves<FDT, MODE>))) void k_push(PushArgs a) {
     push_grid<PREC, FDT, MODE, kFormLane, TAME>(a);
 }
 
-// Latency forms, for fewer active particles than fill the machine: a
-// wavefront's step time is then its chain of instructions and memory round
-// trips.  The all-pairs form (full equations) has each gather of an array in
-// one round trip; the quad form spreads the particles over four times as many
-// wavefronts (and compute units) and interpolates a quarter of the values per
-// lane (quad_limit).
-template <int PREC, int FDT, int MODE, bool TAME>
-__global__ __launch_bounds__(256) void k_push_allpairs(PushArgs a) {
-    push_grid<PREC, FDT, MODE, kFormAllPairs, TAME>(a);
-}
-
+// For fewer active particles than fill the machine (quad_limit): a wavefront's
+// step time is then its chain of instructions and memory round trips; the quad
+// form spreads the particles over four times as many wavefronts (and compute
+// units) and interpolates a quarter of the values per lane.
 template <int PREC, int FDT, int MODE, bool TAME>
 __global__ __launch_bounds__(256) void k_push_quad(PushArgs a) {
     push_grid<PREC, FDT, MODE, kFormQuad, TAME>(a);
@@ -375,22 +352,18 @@ __global__ __launch_bounds__(256) void k_push_quad(PushArgs a) {
 // queueing behind few workgroups.
 //
 // With a tail threshold T = a.tail > 0 each chunk launches the one-lane kernel
-// and the tail kernels its instantiation has (all pairs, quad) in turn, and the
-// live count on the device (written by the reorder) selects the one that works,
-// the others returning at once: below quad_limit the quad form, from there to T
-// all pairs where that form exists, else one lane per particle.  The choice is
-// made on the device so that a captured graph follows the count without a host
-// read-back.  Steps are counted per form (a.steps_done + form), the one-lane
-// form's below T under [1].
+// and the quad kernel in turn, and the live count on the device (written by the
+// reorder) selects the one that works, the other returning at once: the quad
+// form below quad_limit.  The choice is made on the device so that a captured
+// graph follows the count without a host read-back.  Steps are counted per form
+// (a.steps_done + form), the one-lane form's below T under kFormTail.
 template <int PREC, int FDT, int MODE, int FORM, bool TAME = false>
 __device__ __forceinline__ void push_persistent(const PushArgs &a) {
     __shared__ uint32_t s_tile;
     const uint32_t n = *a.n_active;
     const uint32_t T = a.tail;
-    const uint32_t quad = quad_limit(T, PREC == GC_PREC_F64, FDT, MODE == 2, true);
-    const uint32_t lo = FORM == kFormQuad ? 0u : FORM == kFormLane && kHasAllPairs<FDT, MODE> ? T : quad;
-    const uint32_t hi = FORM == kFormLane ? 0xFFFFFFFFu : FORM == kFormAllPairs ? T : quad;
-    if (n < lo || n >= hi) return;
+    const uint32_t quad = quad_limit(T, PREC == GC_PREC_F64, FDT, MODE == 2);
+    if (FORM == kFormQuad ? n >= quad : n < quad) return;
     constexpr uint32_t G = FORM == kFormQuad ? 4 : 1;          // lanes per particle
     const uint32_t per = blockDim.x / G;                       // particles per workgroup round
     const uint32_t share = ((n + gridDim.x - 1) / gridDim.x + per - 1) / per * per;
@@ -407,17 +380,13 @@ __device__ __forceinline__ void push_persistent(const PushArgs &a) {
         for (uint32_t slot = t * tile + threadIdx.x / G; slot < end; slot += per)
             taken += advance_slot<PREC, FDT, MODE, FORM, TAME>(a, slot, threadIdx.x % G);
     }
-    count_steps(a.steps_done + (FORM == kFormLane && n < T ? kFormAllPairs : FORM), taken);
+    count_steps(a.steps_done + (FORM == kFormLane && n < T ? kFormTail : FORM), taken);
 }
 
 template <int PREC, int FDT, int MODE, bool TAME>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_push_persistent(PushArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kLaneWaves<FDT, MODE>)))
+void k_push_persistent(PushArgs a) {
     push_persistent<PREC, FDT, MODE, kFormLane, TAME>(a);
-}
-
-template <int PREC, int FDT, int MODE, bool TAME>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_push_persistent_allpairs(PushArgs a) {
-    push_persistent<PREC, FDT, MODE, kFormAllPairs, TAME>(a);
 }
 
 template <int PREC, int FDT, int MODE, bool TAME>
@@ -428,17 +397,13 @@ __global__ __launch_bounds__(256) void k_push_persistent_quad(PushArgs a) {
 template <int PREC, int FDT, int MODE, bool TAME>
 static hipError_t launch_rt(const PushArgs &a, int block, bool persistent, int form, int grid_blocks, hipStream_t s,
                            LaunchEvents ev) {
+    constexpr bool kQuad = kHasQuad<FDT, MODE>;
     if (persistent) {
-        constexpr bool kPairs = kHasAllPairs<FDT, MODE>, kQuad = kHasQuad<FDT, MODE>;
-        const bool tail = a.tail > 0;
+        const bool quad = kQuad && a.tail > 0;
         launch_timed((k_push_persistent<PREC, FDT, MODE, TAME>), dim3(grid_blocks), dim3(block), s, ev.start,
-                     tail && (kPairs || kQuad) ? nullptr : ev.stop, a);
-        if constexpr (kPairs)
-            if (tail)
-                launch_timed((k_push_persistent_allpairs<PREC, FDT, MODE, TAME>), dim3(grid_blocks), dim3(block), s,
-                             nullptr, kQuad ? nullptr : ev.stop, a);
+                     quad ? nullptr : ev.stop, a);
         if constexpr (kQuad)
-            if (tail)   // 256-thread workgroups (64 particles per round), as the grid quad form
+            if (quad)   // 256-thread workgroups (64 particles per round), as the grid quad form
                 launch_timed((k_push_persistent_quad<PREC, FDT, MODE, TAME>), dim3((uint32_t)grid_blocks * block / 256),
                              dim3(256), s, nullptr, ev.stop, a);
         return hipGetLastError();
@@ -449,12 +414,7 @@ static hipError_t launch_rt(const PushArgs &a, int block, bool persistent, int f
         if (ev.stop) (void)hipEventRecord(ev.stop, s);
         return hipGetLastError();
     }
-    if constexpr (MODE == 2) {
-        if (form != kFormLane) {
-            launch_timed((k_push_allpairs<PREC, FDT, MODE, TAME>), dim3(nb), dim3(block), s, ev.start, ev.stop, a);
-            return hipGetLastError();
-        }
-    } else if constexpr (kHasQuad<FDT, MODE>) {
+    if constexpr (kQuad)
         if (form == kFormQuad) {
             // 256-thread workgroups whatever the block size (64 particles each;
             // measured faster for this form than 64 threads)
@@ -462,7 +422,6 @@ static hipError_t launch_rt(const PushArgs &a, int block, bool persistent, int f
             launch_timed((k_push_quad<PREC, FDT, MODE, TAME>), dim3(qb), dim3(256), s, ev.start, ev.stop, a);
             return hipGetLastError();
         }
-    }
     launch_timed((k_push<PREC, FDT, MODE, TAME>), dim3(nb), dim3(block), s, ev.start, ev.stop, a);
     return hipGetLastError();
 }
