@@ -974,7 +974,8 @@ gc_status gc_count(const gc_ctx *ctx, uint64_t *n) {
 gc_status gc_get_state(gc_ctx *ctx, const gc_state_view *dst) {
     if (!ctx || !dst) return GC_EINVAL;
     HIPCHK(hipSetDevice(ctx->opt.device));
-    HIPCHK(launch_state_out(ctx->A, *dst, (uint32_t)ctx->n, ctx->stream));
+    // (the sort's value buffer is free between the reorders that use it)
+    HIPCHK(launch_state_out(ctx->A, *dst, (uint32_t)ctx->n, ctx->sc.vals[0], ctx->stream));
     return GC_OK;
 }
 

@@ -50,7 +50,8 @@ hipError_t launch_inject(const SoA &st, const FieldDev &f, const EnsDev &e, uint
 hipError_t launch_moments(const SoA &st, const FieldDev &f, const EnsDev *ens, uint32_t n, const MomDev &m,
                           unsigned long long *out, const uint32_t *n_scan, const unsigned long long *dead,
                           hipStream_t s);
-hipError_t launch_state_out(const SoA &st, const gc_state_view &dst, uint32_t n, hipStream_t s);
+// (inv: scratch of n words)
+hipError_t launch_state_out(const SoA &st, const gc_state_view &dst, uint32_t n, uint32_t *inv, hipStream_t s);
 hipError_t launch_state_in(const SoA &st, const gc_state_view &src, uint32_t n, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, size_t n, hipStream_t s);
