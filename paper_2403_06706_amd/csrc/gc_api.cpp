@@ -447,7 +447,7 @@ gc_status push(gc_ctx *ctx, double dt, int32_t steps, bool timed) {
     if (ctx->opt.field_source == GC_SOURCE_MLP) {
         if (moved) return fail(ctx, GC_ESTATE, "the neural-field push does not apply permutations");
         if (timed) HIPCHK(hipEventRecord(e0, s));
-        HIPCHK(launch_push_mlp(a, ctx->mlp.args, ctx->opt.precision, s));
+        HIPCHK(launch_push_mlp(a, ctx->mlp.args, ctx->opt.precision, ctx->n_cus, s));
         if (timed) HIPCHK(hipEventRecord(e1, s));
     } else {
         LaunchEvents ev;
@@ -1528,7 +1528,7 @@ gc_status gc_mlp_eval(gc_ctx *ctx, const double *pts, int64_t n, double *out) {
     gc_status st = check_mlp_points(ctx, pts, n, out);
     if (st != GC_OK || n == 0) return st;
     HIPCHK(hipSetDevice(ctx->opt.device));
-    HIPCHK(mlp_launch_eval(ctx->mlp.args, pts, (int)n, out, ctx->stream));
+    HIPCHK(mlp_launch_eval(ctx->mlp.args, pts, (int)n, out, ctx->n_cus, ctx->stream));
     return GC_OK;
 }
 

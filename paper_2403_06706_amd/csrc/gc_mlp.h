@@ -122,13 +122,40 @@ __device__ __forceinline__ void mlp_store(const u32x4 v[U], __bf16 *dst) {
     }
 }
 
+// Passes of 16 particles per wavefront, 1..4, for n particles on cus compute
+// units that each hold one workgroup of `waves` wavefronts: the fewest passes in a
+// row, a workgroup's other work (assembly, right-hand side, step; one particle per
+// lane) counted as a quarter of one.  With 64 particles per wavefront throughout,
+// 2,000 particles kept 4 of 256 compute units busy.  Evaluation
+// of 5,000 points 96 -> 22 us, 33,000 101 -> 58, 66,000 108 -> 87, 140,000 212 -> 165
+// (100,000 keep four passes); push of 16,000 electrons x 24 steps 5.11 -> 1.15 ms.
+// From four full rounds on, always four passes: at most kMlpShort cus workgroups
+// have fewer.
+constexpr uint32_t kMlpShort = 16;
+__host__ __device__ inline int mlp_passes(uint32_t n, int waves, int cus) {
+    int best = 4;
+    if (n > kMlpShort * 16u * waves * cus) return best;
+    uint32_t cost = 0xFFFFFFFFu;
+    for (int p = 4; p >= 1; --p) {
+        const uint32_t per = 16u * p * waves * cus, c = ((n + per - 1) / per) * (4u * p + 1u);
+        if (c < cost) { cost = c; best = p; }
+    }
+    return best;
+}
+
+// Wavefronts per workgroup: eight (two per SIMD) hide each other's activations and
+// share one staging of the weights; four as long as one wavefront per SIMD and one
+// pass hold every particle.
+__host__ __device__ inline int mlp_waves(uint32_t n, int cus) { return n <= 64u * (uint32_t)cus ? 4 : 8; }
+
 // Evaluate the network and its three tangents for the particles of an
-// NT-thread workgroup (one per thread).  All NT threads must call it together
-// (it synchronizes the workgroup); the biases must be in L (mlp_lds_init).
+// NT-thread workgroup: those of the first 16 `passes` lanes of each wavefront.
+// All NT threads must call it together (it synchronizes the workgroup); the
+// biases must be in L (mlp_lds_init).
 // Output per thread: y[6] and dy[d][6] = dy / d(r, th, ph)[d].
 //
-// Matrix-core tiling (v_mfma_f32_16x16x32_bf16; each wavefront takes its 64
-// particles in 4 passes of 16): the products are taken transposed, Z^T = W H^T,
+// Matrix-core tiling (v_mfma_f32_16x16x32_bf16; each wavefront takes its
+// particles in passes of 16): the products are taken transposed, Z^T = W H^T,
 // so that the weights are the A operand and the activations the B operand.
 // The B operand has four column tiles: the values of the 16 particles and
 // their derivatives along r, th and ph.  In the 16x16 accumulator layout a lane
@@ -142,7 +169,7 @@ __device__ __forceinline__ void mlp_store(const u32x4 v[U], __bf16 *dst) {
 // tiles x 4 k-blocks x 4 column tiles = 128 MFMAs, the products of tile t
 // issued before the activation of tile t - 1, which they overlap.
 template <int NT, int kUnroll = 1>
-__device__ __forceinline__ void mlp_block(const MlpArgs &m, float r, float th, float ph, MlpLds<NT> &L,
+__device__ __forceinline__ void mlp_block(const MlpArgs &m, int passes, float r, float th, float ph, MlpLds<NT> &L,
                                           float y[kMlpOut], float dy[3][kMlpOut]) {
     constexpr int kPer = kMlpPieces / NT;                  // pieces per thread
     constexpr int kHalf = kPer / 2;
@@ -156,7 +183,7 @@ __device__ __forceinline__ void mlp_block(const MlpArgs &m, float r, float th, f
     mlp_fetch<NT, 0, kPer>(m, 0, pf);
     mlp_store<NT, 0, kPer>(pf, L.w[0]);
     int cur = 0;
-    for (int p = 0; p < 4; ++p) {
+    for (int p = 0; p < passes; ++p) {
         const int src = 16 * p + col;                        // the particle of this lane's column
         const float pr = __shfl(r, src), pth = __shfl(th, src), pph = __shfl(ph, src);
         const float rt = (pr - m.r_min) * m.inv_rspan, tt = pth * 0.3183098861837907f;

@@ -416,30 +416,59 @@ __global__ void k_mlp_refresh(const float *p, __bf16 *W, __bf16 *WT, __bf16 *Wo,
 // Point evaluation: neural field (64 points per wavefront) and trilinear grid.
 // pts SoA: r[n], th[n], ph[n]; out: [n][12].
 // ---------------------------------------------------------------------------
-constexpr int kEvalThreads = 512;   // 8 wavefronts (2 per SIMD) share the staged weights
-
-__global__ __launch_bounds__(kEvalThreads) __attribute__((amdgpu_waves_per_eu(2)))
-void k_mlp_eval(MlpArgs m, const double *pts, int n, double *out) {
-    __shared__ MlpLds<kEvalThreads> L;
-    mlp_lds_init(m, L);
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int ii = i < n ? i : n - 1;                 // idle lanes evaluate a valid point
-    const double r = pts[ii], th = pts[n + ii], ph = pts[2 * n + ii];
-    float y[kMlpOut], dy[3][kMlpOut];
-    mlp_block<kEvalThreads>(m, (float)r, (float)th, (float)ph, L, y, dy);
-    double g[12];
-    const bool ok = mlp_assemble<double>(m, r, th, y, dy, g);
-    if (i < n)
-        for (int c = 0; c < 12; ++c) out[(size_t)i * 12 + c] = ok ? g[c] : __builtin_nan("");
+// The twelve components of point i, or NaN, in 16-byte stores (96 bytes a point;
+// the caller's array is aligned to its doubles only).
+__device__ __forceinline__ void store12(double *out, int i, const double g[12], bool ok) {
+    typedef double pair __attribute__((ext_vector_type(2), aligned(8)));
+    const double nan = __builtin_nan("");
+    pair *o = reinterpret_cast<pair *>(out + (size_t)i * 12);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+        pair v;
+        v.x = ok ? g[2 * c] : nan;
+        v.y = ok ? g[2 * c + 1] : nan;
+        o[c] = v;
+    }
 }
 
+// NT = 512: 8 wavefronts (2 per SIMD) share the staged weights; 256 for so few
+// points that one wavefront per SIMD holds them.
+// kPasses: 4, or 0 for the argument's number (a constant count is 1 % faster).
+template <int NT, int kPasses>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 256)))
+void k_mlp_eval(MlpArgs m, int n_passes, const double *pts, int n, double *out) {
+    __shared__ MlpLds<NT> L;
+    mlp_lds_init(m, L);
+    const int passes = kPasses ? kPasses : n_passes;
+    const int lane = threadIdx.x & 63, per = 16 * passes;
+    const int i = (blockIdx.x * (NT / 64) + (threadIdx.x >> 6)) * per + lane;
+    const bool in = lane < per && i < n;
+    const int ii = in ? i : n - 1;                    // idle lanes evaluate a valid point
+    const double r = pts[ii], th = pts[(size_t)n + ii], ph = pts[2 * (size_t)n + ii];
+    float y[kMlpOut], dy[3][kMlpOut];
+    mlp_block<NT>(m, passes, (float)r, (float)th, (float)ph, L, y, dy);
+    double g[12];
+    const bool ok = mlp_assemble<double>(m, r, th, y, dy, g);
+    if (in) store12(out, i, g, ok);
+}
+
+// One point per lane, the eight nodes of its cell in flight at once; workgroups of
+// one wavefront, so that a training batch (16,384 points) spreads over every
+// compute unit: 16.3 -> 6.9 us.
 template <int FDT>
-__global__ void k_field_sample(FieldDev f, const double *pts, int n, double *out) {
+__global__ __launch_bounds__(64) void k_field_sample(FieldDev f, const double *pts, int n, double *out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
+    CellPos<double> at;
+    LaneCell<FDT> cell;
+    NoCell none;
     double g[12];
-    const bool ok = gather<FDT, double>(f, pts[i], pts[n + i], pts[2 * n + i], g);
-    for (int c = 0; c < 12; ++c) out[(size_t)i * 12 + c] = ok ? g[c] : __builtin_nan("");
+    bool ok = cell_seek<FDT, double>(f, pts[i], pts[(size_t)n + i], pts[2 * (size_t)n + i], 0u, at, cell, f, none);
+    if (ok) {
+        cell.template value<0, 12, double>(f, at, 0u, g);
+        ok = finite12(g);
+    }
+    store12(out, i, g, ok);
 }
 
 // ---------------------------------------------------------------------------
@@ -467,16 +496,19 @@ hipError_t mlp_launch_refresh(const float *p, __bf16 *W, __bf16 *WT, __bf16 *Wo,
     return hipGetLastError();
 }
 
-hipError_t mlp_launch_eval(const MlpArgs &m, const double *pts, int n, double *out, hipStream_t s) {
+hipError_t mlp_launch_eval(const MlpArgs &m, const double *pts, int n, double *out, int cus, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_eval, dim3((n + kEvalThreads - 1) / kEvalThreads), dim3(kEvalThreads), 0, s, m, pts, n,
-                       out);
+    const int waves = mlp_waves(n, cus), passes = mlp_passes(n, waves, cus), per = 16 * passes * waves;
+    const dim3 grid((n + per - 1) / per);
+    if (waves == 4) hipLaunchKernelGGL((k_mlp_eval<256, 0>), grid, dim3(256), 0, s, m, passes, pts, n, out);
+    else if (passes == 4) hipLaunchKernelGGL((k_mlp_eval<512, 4>), grid, dim3(512), 0, s, m, passes, pts, n, out);
+    else hipLaunchKernelGGL((k_mlp_eval<512, 0>), grid, dim3(512), 0, s, m, passes, pts, n, out);
     return hipGetLastError();
 }
 
 hipError_t launch_field_sample(const FieldDev &f, const double *pts, int n, double *out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const dim3 grid((n + 255) / 256), block(256);
+    const dim3 grid((n + 63) / 64), block(64);
     switch (f.dtype) {
         case GC_F64: hipLaunchKernelGGL(k_field_sample<GC_F64>, grid, block, 0, s, f, pts, n, out); break;
         case GC_F32: hipLaunchKernelGGL(k_field_sample<GC_F32>, grid, block, 0, s, f, pts, n, out); break;

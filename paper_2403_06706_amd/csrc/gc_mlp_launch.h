@@ -48,8 +48,8 @@ hipError_t mlp_launch_train(const MlpArgs &m, const TrainNet &net, const double 
                             hipStream_t s);
 hipError_t mlp_launch_refresh(const float *p, __bf16 *W, __bf16 *WT, __bf16 *Wo, __bf16 *We, __bf16 *Woe,
                               hipStream_t s);
-hipError_t mlp_launch_eval(const MlpArgs &m, const double *pts, int n, double *out, hipStream_t s);
+hipError_t mlp_launch_eval(const MlpArgs &m, const double *pts, int n, double *out, int cus, hipStream_t s);
 hipError_t launch_field_sample(const FieldDev &f, const double *pts, int n, double *out, hipStream_t s);
-hipError_t launch_push_mlp(const PushArgs &a, const MlpArgs &m, int precision, hipStream_t s);
+hipError_t launch_push_mlp(const PushArgs &a, const MlpArgs &m, int precision, int cus, hipStream_t s);
 
 }  // namespace gc
