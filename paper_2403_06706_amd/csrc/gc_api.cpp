@@ -299,8 +299,8 @@ uint32_t bits_for(uint32_t max_key) {
 // Then the push takes a latency form (below quad_limit four lanes per
 // particle, else all loads of a gather in flight), and the reorder runs only
 // every kTailReorderEvery chunks (particles cross about two
-// cells per 64 steps, so the cell order decays slowly, while a reorder costs a
-// fixed ~70 us of launches).  No choice changes any particle's trajectory.
+// cells per 64 steps, so the cell order decays slowly, while a reorder costs
+// 13 us up to 4,096 particles and 40 us of launches past that).  No choice changes any particle's trajectory.
 constexpr int kTailReorderEvery = 8;
 // The live count read back is only as fresh as the host's lead over the
 // device: with the tail policy on, the host issues a chunk only once the chunk
@@ -362,9 +362,10 @@ gc_status reorder(gc_ctx *ctx, bool timed, int order) {
         e1 = take_event(ctx);
     }
     const bool comp = ctx->opt.precision == GC_PREC_F32_KAHAN;
+    const bool grid = ctx->opt.field_source == GC_SOURCE_GRID;
     uint32_t *perm = nullptr;
     if (order == GC_ORDER_COMPACT) {
-        HIPCHK(launch_compact(ctx->A, ctx->n_bound, n, ctx->sc, ctx->n_active, &perm, s, e0));
+        HIPCHK(launch_compact(ctx->A, ctx->n_bound, n, ctx->sc, ctx->n_active, ctx->sorted_n, &perm, s, e0));
     } else {
         const int c = ctx->opt.bin_coarsen;
         const uint32_t nrc = ((uint32_t)ctx->f.nr + (1u << c) - 1) >> c;
@@ -373,15 +374,17 @@ gc_status reorder(gc_ctx *ctx, bool timed, int order) {
         const uint32_t dead = nrc * nthc * nphc;
         ctx->sorted_dead = dead;
         const int bits = (int)bits_for(dead);
-        HIPCHK(launch_cell_keys(ctx->A, ctx->f, ctx->n_bound, n, c, dead, bits, ctx->sc, ctx->n_active, s, e0));
-        HIPCHK(launch_radix_sort(ctx->sc, ctx->n_bound, n, bits, ctx->n_active, &perm, s));
+        HIPCHK(launch_cell_sort(ctx->A, ctx->f, ctx->n_bound, n, c, dead, bits, ctx->sc, ctx->n_active, ctx->sorted_n,
+                                grid ? &ctx->B : nullptr, comp, &perm, s, e0));
     }
-    if (ctx->opt.field_source == GC_SOURCE_GRID) {
+    if (grid) {
         // The grid push applies the permutation itself (it reads every active
         // particle from A through perm and writes it to B): here only the
         // particles stopped since the last reorder, slots [n_active, n_bound)
-        // of the new order, move; the push ends the reorder.
-        HIPCHK(launch_permute(ctx->A, ctx->B, perm, ctx->n_active, ctx->n_bound, n, comp, s));
+        // of the new order, move (the cell sort has moved them already); the
+        // push ends the reorder.
+        if (order == GC_ORDER_COMPACT)
+            HIPCHK(launch_permute(ctx->A, ctx->B, perm, ctx->n_active, ctx->n_bound, n, comp, s));
         ctx->pend_perm = perm;
         ctx->pend_order = order;
         ctx->pend_e0 = e0;
@@ -402,8 +405,8 @@ gc_status finish_reorder(gc_ctx *ctx, int order, hipEvent_t e0, hipEvent_t e1, h
     hipStream_t s = ctx->stream;
     const uint32_t n = (uint32_t)ctx->n;
     const bool comp = ctx->opt.precision == GC_PREC_F32_KAHAN;
-    HIPCHK(launch_copy_range(ctx->B, ctx->A, ctx->n_active, ctx->n_bound, n, comp, ctx->dead, s));
-    HIPCHK(launch_copy_count(ctx->n_bound, ctx->n_active, ctx->count_host, ctx->sorted_n, ctx->sc.state, s, e1));
+    HIPCHK(launch_end_reorder(ctx->B, ctx->A, ctx->n_active, ctx->sorted_n, n, comp, ctx->dead, ctx->n_bound,
+                              ctx->count_host, ctx->sc.state, s, e1));
     ctx->order_known = true;
     ctx->keys_known = order == GC_ORDER_BIN;
     std::swap(ctx->A, ctx->B);
@@ -996,7 +999,7 @@ gc_status gc_set_state(gc_ctx *ctx, const gc_state_view *src, uint64_t n) {
     // look-back tags behind (the reset also moves the tags to a new epoch)
     if (ctx->sc.state) {
         HIPCHK(launch_fill_u32(ctx->sc.state + kStError, 0u, 1, ctx->stream));
-        HIPCHK(launch_copy_count(ctx->n_bound, ctx->n_active, nullptr, nullptr, ctx->sc.state, ctx->stream));
+        HIPCHK(launch_reset_sort(ctx->sc.state, ctx->stream));
     }
     if (ctx->pend_perm) {
         ctx->pend_perm = nullptr;

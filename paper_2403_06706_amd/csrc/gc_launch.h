@@ -60,7 +60,7 @@ hipError_t launch_pack_field(const double *src, void *dst, int nr, int nth, int 
                              const float *inv_scale, hipStream_t s);
 
 // reordering (gc_order.hip)
-constexpr int kSortTile = 2048;     // items per radix-sort tile (one workgroup)
+constexpr int kSortTile = 4096;     // items per radix-sort tile (one workgroup)
 constexpr int kMaxPasses = 4;       // 8-bit digits of a 32-bit key
 // Sort state (uint32 words), zero when a context allocates it; the reset at the
 // end of every reorder clears the counts and tickets and advances the epoch.
@@ -82,30 +82,31 @@ struct OrderScratch {
 };
 // Reorder kernels act on the live prefix [0, *np) of the slots (np in device
 // memory); n_max (host) is an upper bound used to size the grids.
-// cell keys of the live prefix into sc.keys[0], with the digit counts of every
-// pass of a bits-wide sort and the active count added to sc.state
-hipError_t launch_cell_keys(const SoA &st, const FieldDev &f, const uint32_t *np, uint32_t n_max, int coarsen,
-                            uint32_t dead_key, int bits, OrderScratch &sc, uint32_t *n_active, hipStream_t s,
+// stable sort of the live prefix by cell key (the low bits of the keys, inactive
+// particles dead_key): perm_out = the sorted slots, sc.sorted_keys their keys,
+// *n_active = the active count, *sorted_n = *np; with stopped set, the
+// particles of the slots [*n_active, *np) of the new order move there from st
+hipError_t launch_cell_sort(const SoA &st, const FieldDev &f, const uint32_t *np, uint32_t n_max, int coarsen,
+                            uint32_t dead_key, int bits, OrderScratch &sc, uint32_t *n_active, uint32_t *sorted_n,
+                            const SoA *stopped, bool with_comp, uint32_t **perm_out, hipStream_t s,
                             hipEvent_t start = nullptr);
-// stable sort of (sc.keys[0], slot) by the low bits of the keys from launch_cell_keys;
-// *n_active = the active count; perm_out: sorted slots
-hipError_t launch_radix_sort(OrderScratch &sc, const uint32_t *np, uint32_t n_max, int bits, uint32_t *n_active,
-                             uint32_t **perm_out, hipStream_t s);
+// stable partition of the live prefix, active first; outputs as above
 hipError_t launch_compact(const SoA &st, const uint32_t *np, uint32_t n_max, OrderScratch &sc, uint32_t *n_active,
-                          uint32_t **perm_out, hipStream_t s, hipEvent_t start = nullptr);
+                          uint32_t *sorted_n, uint32_t **perm_out, hipStream_t s, hipEvent_t start = nullptr);
 // dst[i] = src[perm[i]] for i in [*lo, *hi) (lo null: from 0)
 hipError_t launch_permute(const SoA &src, const SoA &dst, const uint32_t *perm, const uint32_t *lo,
                           const uint32_t *hi, uint32_t n_max, bool with_comp, hipStream_t s);
-// dst[i] = src[i] for i in [*lo, *hi); with dead set, the per-status counts,
-// collision counts and steps of those slots are added to dead[0..5]
-hipError_t launch_copy_range(const SoA &src, const SoA &dst, const uint32_t *lo, const uint32_t *hi, uint32_t n_max,
-                             bool with_comp, unsigned long long *dead, hipStream_t s);
+// the end of a reorder, src the new state: dst[i] = src[i] for i in [*n_active,
+// *sorted_n), their per-status counts, collision counts and steps added to
+// dead[0..5]; *n_bound = *n_active, also *host_mirror when set (host-coherent
+// pinned memory); the sort state reset for the next reorder
+hipError_t launch_end_reorder(const SoA &src, const SoA &dst, const uint32_t *n_active, const uint32_t *sorted_n,
+                              uint32_t n_max, bool with_comp, unsigned long long *dead, uint32_t *n_bound,
+                              volatile uint32_t *host_mirror, uint32_t *sort_state, hipStream_t s,
+                              hipEvent_t stop = nullptr);
+hipError_t launch_reset_sort(uint32_t *sort_state, hipStream_t s);
 // *n_bound = n and dead[0..5] = 0: the live prefix is every slot again
 hipError_t launch_reset_bound(uint32_t *n_bound, uint32_t n, unsigned long long *dead, hipStream_t s);
-// *dst = *src; also *host_mirror = *src when host_mirror (host-coherent pinned memory) is set,
-// and *prev = the old *dst when prev is set; then resets the sort state for the next reorder
-hipError_t launch_copy_count(uint32_t *dst, const uint32_t *src, volatile uint32_t *host_mirror, uint32_t *prev,
-                             uint32_t *sort_state, hipStream_t s, hipEvent_t stop = nullptr);
 // out[i] = i < *sorted_n ? sorted_keys[i] : dead_key for i < n
 hipError_t launch_keys_out(const uint32_t *sorted_keys, const uint32_t *sorted_n, uint32_t dead_key, uint32_t n,
                            uint32_t *out, hipStream_t s);
