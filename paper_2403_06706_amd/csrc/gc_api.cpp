@@ -300,7 +300,8 @@ uint32_t bits_for(uint32_t max_key) {
 // particle, else all loads of a gather in flight), and the reorder runs only
 // every kTailReorderEvery chunks (particles cross about two
 // cells per 64 steps, so the cell order decays slowly, while a reorder costs
-// 13 us up to 4,096 particles and 40 us of launches past that).  No choice changes any particle's trajectory.
+// 13 us up to 4,096 particles and 40 us of launches past that).  No choice
+// changes any particle's trajectory.
 constexpr int kTailReorderEvery = 8;
 // The live count read back is only as fresh as the host's lead over the
 // device: with the tail policy on, the host issues a chunk only once the chunk

@@ -122,25 +122,36 @@ __device__ __forceinline__ void mlp_store(const u32x4 v[U], __bf16 *dst) {
     }
 }
 
-// Passes of 16 particles per wavefront, 1..4, for n particles on cus compute
-// units that each hold one workgroup of `waves` wavefronts: the fewest passes in a
-// row, a workgroup's other work (assembly, right-hand side, step; one particle per
-// lane) counted as a quarter of one.  With 64 particles per wavefront throughout,
-// 2,000 particles kept 4 of 256 compute units busy.  Evaluation
-// of 5,000 points 96 -> 22 us, 33,000 101 -> 58, 66,000 108 -> 87, 140,000 212 -> 165
-// (100,000 keep four passes); push of 16,000 electrons x 24 steps 5.11 -> 1.15 ms.
-// From four full rounds on, always four passes: at most kMlpShort cus workgroups
-// have fewer.
-constexpr uint32_t kMlpShort = 16;
-__host__ __device__ inline int mlp_passes(uint32_t n, int waves, int cus) {
-    int best = 4;
+// Half passes of a workgroup, 2..8, for n particles on cus compute units that each
+// hold one workgroup of `waves` wavefronts: with h half passes its first half of the
+// wavefronts takes (h + 1) / 2 passes of 16 particles and the second h / 2
+// (mlp_share), so that of eight wavefronts, two to a SIMD, each SIMD has h passes.
+// The choice is the fewest passes in a row, counted in eighths of a pass of both
+// wavefronts: a last pass of the first half alone takes kMlpAlone of them, a
+// workgroup's other work (assembly, right-hand side, step; one particle per lane) two.
+// With 64 particles per wavefront throughout, 2,000 particles kept 4 of 256 compute
+// units busy, and 100,000 196.  Evaluation of 5,000 points 96 -> 22 us, 33,000
+// 101 -> 58, 66,000 108 -> 87, 140,000 212 -> 165; push of 16,000 electrons x 24 steps
+// 5.11 -> 1.15 ms, of 100,000 5.40 -> 5.12 (224 workgroups of seven half passes).
+// From four full rounds on, always eight: at most kMlpShort cus workgroups have fewer.
+constexpr uint32_t kMlpShort = 16, kMlpAlone = 6;
+__host__ __device__ inline int mlp_halves(uint32_t n, int waves, int cus) {
+    int best = 8;
     if (n > kMlpShort * 16u * waves * cus) return best;
     uint32_t cost = 0xFFFFFFFFu;
-    for (int p = 4; p >= 1; --p) {
-        const uint32_t per = 16u * p * waves * cus, c = ((n + per - 1) / per) * (4u * p + 1u);
-        if (c < cost) { cost = c; best = p; }
+    for (int h = 8; h >= 2; h -= waves == 8 ? 1 : 2) {
+        const uint32_t per = 8u * h * waves * cus;
+        const uint32_t c = ((n + per - 1) / per) * (8u * (h / 2) + (h & 1 ? kMlpAlone : 0u) + 2u);
+        if (c < cost) { cost = c; best = h; }
     }
     return best;
+}
+// The particles of a wavefront: passes of 16, the first at `first` of the workgroup's 8 waves h.
+struct MlpShare { int passes; uint32_t first; };
+__device__ __forceinline__ MlpShare mlp_share(int halves, int waves) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), late = max(wave - waves / 2, 0);
+    const int more = (halves + 1) / 2, fewer = halves / 2;
+    return {wave < waves / 2 ? more : fewer, 16u * (uint32_t)((wave - late) * more + late * fewer)};
 }
 
 // Wavefronts per workgroup: eight (two per SIMD) hide each other's activations and
@@ -149,7 +160,8 @@ __host__ __device__ inline int mlp_passes(uint32_t n, int waves, int cus) {
 __host__ __device__ inline int mlp_waves(uint32_t n, int cus) { return n <= 64u * (uint32_t)cus ? 4 : 8; }
 
 // Evaluate the network and its three tangents for the particles of an
-// NT-thread workgroup: those of the first 16 `passes` lanes of each wavefront.
+// NT-thread workgroup: those of the first lanes of each wavefront, 16 per pass of
+// its share (mlp_share).
 // All NT threads must call it together (it synchronizes the workgroup); the
 // biases must be in L (mlp_lds_init).
 // Output per thread: y[6] and dy[d][6] = dy / d(r, th, ph)[d].
@@ -169,7 +181,7 @@ __host__ __device__ inline int mlp_waves(uint32_t n, int cus) { return n <= 64u 
 // tiles x 4 k-blocks x 4 column tiles = 128 MFMAs, the products of tile t
 // issued before the activation of tile t - 1, which they overlap.
 template <int NT, int kUnroll = 1>
-__device__ __forceinline__ void mlp_block(const MlpArgs &m, int passes, float r, float th, float ph, MlpLds<NT> &L,
+__device__ __forceinline__ void mlp_block(const MlpArgs &m, int halves, float r, float th, float ph, MlpLds<NT> &L,
                                           float y[kMlpOut], float dy[3][kMlpOut]) {
     constexpr int kPer = kMlpPieces / NT;                  // pieces per thread
     constexpr int kHalf = kPer / 2;
@@ -183,7 +195,19 @@ __device__ __forceinline__ void mlp_block(const MlpArgs &m, int passes, float r,
     mlp_fetch<NT, 0, kPer>(m, 0, pf);
     mlp_store<NT, 0, kPer>(pf, L.w[0]);
     int cur = 0;
+    const int passes = (halves + 1) / 2, share = mlp_share(halves, NT / 64).passes;
     for (int p = 0; p < passes; ++p) {
+        if (p >= share) {
+            // a pass of the first half of the wavefronts alone (uniform over the
+            // wavefront): this one only stages its pieces of the weights
+            for (int mi = 0; mi <= kMlpDepth; ++mi) {
+                __syncthreads();
+                mlp_fetch<NT, 0, kPer>(m, mi < kMlpDepth ? mi + 1 : 0, pf);
+                mlp_store<NT, 0, kPer>(pf, L.w[cur ^ 1]);
+                cur ^= 1;
+            }
+            break;
+        }
         const int src = 16 * p + col;                        // the particle of this lane's column
         const float pr = __shfl(r, src), pth = __shfl(th, src), pph = __shfl(ph, src);
         const float rt = (pr - m.r_min) * m.inv_rspan, tt = pth * 0.3183098861837907f;

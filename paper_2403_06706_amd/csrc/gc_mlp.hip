@@ -433,20 +433,21 @@ __device__ __forceinline__ void store12(double *out, int i, const double g[12], 
 
 // NT = 512: 8 wavefronts (2 per SIMD) share the staged weights; 256 for so few
 // points that one wavefront per SIMD holds them.
-// kPasses: 4, or 0 for the argument's number (a constant count is 1 % faster).
-template <int NT, int kPasses>
+// kHalves: 8, or 0 for the argument's number (a constant count is 1 % faster).
+template <int NT, int kHalves>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 256)))
-void k_mlp_eval(MlpArgs m, int n_passes, const double *pts, int n, double *out) {
+void k_mlp_eval(MlpArgs m, int n_halves, const double *pts, int n, double *out) {
     __shared__ MlpLds<NT> L;
     mlp_lds_init(m, L);
-    const int passes = kPasses ? kPasses : n_passes;
-    const int lane = threadIdx.x & 63, per = 16 * passes;
-    const int i = (blockIdx.x * (NT / 64) + (threadIdx.x >> 6)) * per + lane;
-    const bool in = lane < per && i < n;
+    const int halves = kHalves ? kHalves : n_halves;
+    const MlpShare share = mlp_share(halves, NT / 64);
+    const int lane = threadIdx.x & 63;
+    const int i = blockIdx.x * (NT / 8 * halves) + (int)share.first + lane;
+    const bool in = lane < 16 * share.passes && i < n;
     const int ii = in ? i : n - 1;                    // idle lanes evaluate a valid point
     const double r = pts[ii], th = pts[(size_t)n + ii], ph = pts[2 * (size_t)n + ii];
     float y[kMlpOut], dy[3][kMlpOut];
-    mlp_block<NT>(m, passes, (float)r, (float)th, (float)ph, L, y, dy);
+    mlp_block<NT>(m, halves, (float)r, (float)th, (float)ph, L, y, dy);
     double g[12];
     const bool ok = mlp_assemble<double>(m, r, th, y, dy, g);
     if (in) store12(out, i, g, ok);
@@ -498,11 +499,11 @@ hipError_t mlp_launch_refresh(const float *p, __bf16 *W, __bf16 *WT, __bf16 *Wo,
 
 hipError_t mlp_launch_eval(const MlpArgs &m, const double *pts, int n, double *out, int cus, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const int waves = mlp_waves(n, cus), passes = mlp_passes(n, waves, cus), per = 16 * passes * waves;
+    const int waves = mlp_waves(n, cus), halves = mlp_halves(n, waves, cus), per = 8 * halves * waves;
     const dim3 grid((n + per - 1) / per);
-    if (waves == 4) hipLaunchKernelGGL((k_mlp_eval<256, 0>), grid, dim3(256), 0, s, m, passes, pts, n, out);
-    else if (passes == 4) hipLaunchKernelGGL((k_mlp_eval<512, 4>), grid, dim3(512), 0, s, m, passes, pts, n, out);
-    else hipLaunchKernelGGL((k_mlp_eval<512, 0>), grid, dim3(512), 0, s, m, passes, pts, n, out);
+    if (waves == 4) hipLaunchKernelGGL((k_mlp_eval<256, 0>), grid, dim3(256), 0, s, m, halves, pts, n, out);
+    else if (halves == 8) hipLaunchKernelGGL((k_mlp_eval<512, 8>), grid, dim3(512), 0, s, m, halves, pts, n, out);
+    else hipLaunchKernelGGL((k_mlp_eval<512, 0>), grid, dim3(512), 0, s, m, halves, pts, n, out);
     return hipGetLastError();
 }
 

@@ -19,7 +19,7 @@ namespace gc {
 // ---------------------------------------------------------------------------
 // NT = 512: 8 wavefronts (2 per SIMD) share the staged weights; 256 for so few
 // particles that one wavefront per SIMD holds them (mlp_waves).  Each wavefront
-// takes 16 to 64 particles (mlp_passes, from the live count).
+// takes 16 to 64 particles (mlp_halves, from the live count).
 template <int PREC, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 256)))
 void k_push_mlp(PushArgs a, MlpArgs m, int cus) {
@@ -29,16 +29,17 @@ void k_push_mlp(PushArgs a, MlpArgs m, int cus) {
     __shared__ MlpLds<NT> L;
     const uint32_t n = *a.n_active;
     if (n == 0) return;
-    const int passes = mlp_passes(n, NT / 64, cus);
-    const uint32_t per = 16u * passes;                        // particles per wavefront
-    const uint32_t nb = (n + per * (NT / 64) - 1) / (per * (NT / 64)), bidx = blockIdx.x;
+    const int halves = mlp_halves(n, NT / 64, cus);
+    const MlpShare share = mlp_share(halves, NT / 64);
+    const uint32_t per = NT / 8 * halves;                     // particles per workgroup
+    const uint32_t nb = (n + per - 1) / per, bidx = blockIdx.x;
     if (bidx >= nb) return;                                   // whole workgroup idle
     mlp_lds_init(m, L);
     const uint32_t q8 = nb >> 3, rem = nb & 7u, xcd = bidx & 7u, pos = bidx >> 3;
     const uint32_t lb = (xcd < rem ? xcd * (q8 + 1) : rem * (q8 + 1) + (xcd - rem) * q8) + pos;
-    const uint32_t lane = threadIdx.x & 63u, slot = (lb * (NT / 64) + (threadIdx.x >> 6)) * per + lane;
+    const uint32_t lane = threadIdx.x & 63u, slot = lb * per + share.first + lane;
     const SoA &st = a.st;
-    const bool in_range = lane < per && slot < n;
+    const bool in_range = lane < 16u * share.passes && slot < n;
     const uint32_t ls = in_range ? slot : n - 1;              // lanes past the prefix read a valid slot
     uint32_t status = st.status[ls];
     bool alive = in_range && status == GC_ACTIVE;
@@ -79,7 +80,7 @@ void k_push_mlp(PushArgs a, MlpArgs m, int cus) {
     int stage = 0;
     while (__syncthreads_or(active)) {                        // uniform over the workgroup
         float y[kMlpOut], dy[3][kMlpOut];
-        mlp_block<NT, kMlpDepth + 1>(m, passes, (float)px, (float)pth, (float)pph, L, y, dy);
+        mlp_block<NT, kMlpDepth + 1>(m, halves, (float)px, (float)pth, (float)pph, L, y, dy);
         if (!active) continue;
         R g[12];
         if (!mlp_assemble<R>(m, px, pth, y, dy, g)) { status = GC_NONFINITE; active = false; continue; }
@@ -184,7 +185,7 @@ template <int PREC>
 static hipError_t launch_mlp_t(const PushArgs &a, const MlpArgs &m, int cus, hipStream_t s) {
     if (a.n_slots == 0) return hipSuccess;
     const int waves = mlp_waves(a.n_slots, cus);
-    // workgroups for any live count up to n_slots (mlp_passes): 64 particles per
+    // workgroups for any live count up to n_slots (mlp_halves): 64 particles per
     // wavefront, or up to kMlpShort workgroups per compute unit of fewer
     const uint32_t full = (a.n_slots + 64u * waves - 1) / (64u * waves), one = (a.n_slots + 16u * waves - 1) / (16u * waves);
     const uint32_t nb = max(full, min(one, kMlpShort * (uint32_t)cus));
