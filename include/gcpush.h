@@ -90,9 +90,9 @@ typedef struct {
     int32_t field_source;   /* GC_SOURCE_GRID (trilinear grid) or GC_SOURCE_MLP (neural field, gc_mlp_set) */
     int32_t tail_threshold; /* grid form, eager gc_advance: chunks whose live count (as read back from an
                                earlier reorder, at most the number of particles) is below this reorder
-                               only every 8 chunks, and the push may use four lanes per particle
-                               (below a share of it that depends on the precision and the field's
-                               type); 0 disables.
+                               only every 8 chunks, and the push may use two or four lanes per
+                               particle (at shares of it that depend on the precision and the
+                               field's type); 0 disables.
                                Persistent form (also in gc_advance_graph): the device picks such
                                forms from the live count of the chunk's reorder.
                                Results are bitwise identical in every form.  While it is > 0,
@@ -342,7 +342,7 @@ gc_status gc_get_order(gc_ctx *ctx, uint32_t *slot_gid, uint32_t *slot_key, uint
  * with timing = 1; particle_steps: steps taken by active
  * particles since the context was created or counters were reset.  form_*: the
  * same split by form of the grid push: [0] throughput form (and the
- * neural-field push), [1] the tail with one lane per particle, [2] four lanes per
+ * neural-field push), [1] the tail with one or two lanes per particle, [2] four lanes per
  * particle (tail_threshold).  The persistent push splits its steps by form the
  * same way (the device picks the form from the live count) and books the time
  * of its launches under [0].  GC_EDEVICE if a cell-binning sort pass recorded

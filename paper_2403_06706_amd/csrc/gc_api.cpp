@@ -296,10 +296,9 @@ uint32_t bits_for(uint32_t max_key) {
 // Tail of a run (eager advance only): once the live count read back from an
 // earlier reorder is below tail_threshold, the machine is far from full and the
 // push is bound by each wavefront's chain of dependent memory round trips.
-// Then the push takes a latency form (below quad_limit four lanes per
-// particle, else all loads of a gather in flight), and the reorder runs only
-// every kTailReorderEvery chunks (particles cross about two
-// cells per 64 steps, so the cell order decays slowly, while a reorder costs
+// Then the push takes the form of tail_lanes (one, two or four lanes per
+// particle), and the reorder runs only every kTailReorderEvery chunks (particles
+// cross about two cells per 64 steps, so the cell order decays slowly, while a reorder costs
 // 13 us up to 4,096 particles and 40 us of launches past that).  No choice
 // changes any particle's trajectory.
 constexpr int kTailReorderEvery = 8;
@@ -335,7 +334,8 @@ int push_form(const gc_ctx *ctx) {
     const uint32_t n = live_bound(ctx), T = (uint32_t)ctx->opt.tail_threshold;
     if (n >= T) return 0;
     const bool f64 = ctx->opt.precision == GC_PREC_F64, full = ctx->fx.data != nullptr;
-    return n < quad_limit(T, f64, ctx->f.dtype, full) ? 2 : 1;
+    const int lanes = tail_lanes(n, T, f64, ctx->f.dtype, full);
+    return lanes == 4 ? 2 : lanes == 2 ? 3 : 1;
 }
 
 gc_status finish_reorder(gc_ctx *ctx, int order, hipEvent_t e0, hipEvent_t e1, hipEvent_t p0, hipEvent_t p1);
@@ -432,7 +432,8 @@ gc_status push(gc_ctx *ctx, double dt, int32_t steps, bool timed) {
     a.n_slots = (uint32_t)ctx->n;
     a.n_steps = steps;
     a.dt = dt;
-    const int form = ctx->opt.field_source == GC_SOURCE_MLP || ctx->opt.persistent ? 0 : push_form(ctx);
+    const int run = ctx->opt.field_source == GC_SOURCE_MLP || ctx->opt.persistent ? 0 : push_form(ctx);
+    const int form = run == 3 ? 1 : run;            // (two lanes per particle count as the tail's one)
     a.steps_done = ctx->steps + form;
     a.log = ctx->log;
     a.log_depth = ctx->opt.log_depth;
@@ -457,7 +458,7 @@ gc_status push(gc_ctx *ctx, double dt, int32_t steps, bool timed) {
         LaunchEvents ev;
         ev.start = e0;
         ev.stop = e1;
-        HIPCHK(launch_push(a, ctx->opt.precision, ctx->opt.block_size, pers, form, grid_blocks, s, ev));
+        HIPCHK(launch_push(a, ctx->opt.precision, ctx->opt.block_size, pers, run, grid_blocks, s, ev));
     }
     if (timed) ctx->ev_push.push_back({e0, e1, form});
     if (moved) {

@@ -296,74 +296,73 @@ struct LaneCell {
     }
 };
 
-// Word j of lane J of an aligned group of four lanes, to every lane of the
-// group (DPP quad permutation [J, J, J, J]).
-template <int J>
-__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, J * 0x55, 0xF, 0xF, true);
-}
-
-// A value of lane J of an aligned quad, to every lane of the quad.
-template <int J, typename R>
-__device__ __forceinline__ R quad_bcast_value(R x) {
-    static_assert(sizeof(R) % 4 == 0, "whole words");
+// A value of lane J of an aligned group of G = 2 or 4 lanes, to every lane of the
+// group (DPP quad permutations [J, J, J, J], or [J, J, J + 2, J + 2]).
+template <int G, int J, typename R>
+__device__ __forceinline__ R group_bcast(R x) {
+    static_assert(sizeof(R) % 4 == 0 && (G == 2 || G == 4) && J < G, "whole words, lanes of the group");
+    constexpr int kPerm = G == 4 ? J * 0x55 : J | J << 2 | (J + 2) << 4 | (J + 2) << 6;
     uint32_t w[sizeof(R) / 4];
     __builtin_memcpy(w, &x, sizeof w);
 #pragma unroll
-    for (int i = 0; i < (int)(sizeof(R) / 4); ++i) w[i] = quad_bcast<J>(w[i]);
+    for (int i = 0; i < (int)(sizeof(R) / 4); ++i)
+        w[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)w[i], kPerm, 0xF, 0xF, true);
     R y;
     __builtin_memcpy(&y, w, sizeof w);
     return y;
 }
 
-// The nodes of a cell, four lanes of an aligned quad per particle (FP32 and
-// FP64 fields): lane gl keeps components 3gl..3gl+2 (node h of pair p at
-// v[p][3 h + c], from the node records, whose phi pairs are adjacent, 48 or 96
-// bytes each), runs their chains with the operations and order of gather_add,
-// and the quad exchanges the finished components, so all four lanes hold the
-// bits of gather().  Each lane converts and multiplies a quarter of the values.
-// All four lanes must call value together.
-template <int FDT>
-struct QuadCell {
+// The nodes of a cell, an aligned group of G = 2 or 4 lanes per particle (FP32 and
+// FP64 fields): lane gl keeps the N = 12 / G components from N gl on (node h of
+// pair p at v[p][N h + c], from the node records, whose phi pairs are adjacent, 48
+// or 96 bytes each), runs their chains with the operations and order of gather_add,
+// and the group exchanges the finished components, so all its lanes hold the bits
+// of gather().  Each lane converts and multiplies its share of the values.  All
+// lanes of the group must call value together.
+template <int FDT, int G>
+struct GroupCell {
     using T = typename std::conditional<FDT == GC_F64, double, float>::type;
-    T v[4][6];
+    static constexpr int N = 12 / G;
+    T v[4][2 * N];
     template <typename R>
     __device__ __forceinline__ void load(const FieldDev &f, const GatherPlan<R> &gp, uint32_t gl) {
         const uint32_t row = (uint32_t)(f.nph + 1) * 12u;             // theta stride of the records
         const uint32_t o[4] = {gp.rec, gp.rec + row, gp.rec + (uint32_t)f.nth * row, gp.rec + (uint32_t)f.nth * row + row};
-        // per-lane 64-bit addresses: the three components of a node merge into one
-        // load and the second node is a constant offset from the first
-        const T *base = static_cast<const T *>(f.rec) + 3u * gl;
+        // per-lane 64-bit addresses: the components of a node merge into wide loads
+        // and the second node is a constant offset from the first
+        const T *base = static_cast<const T *>(f.rec) + N * gl;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const T *p = base + o[q];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
+            for (int c = 0; c < N; ++c) {
                 v[q][c] = p[c];            // node k
-                v[q][3 + c] = p[12 + c];   // node k + 1
+                v[q][N + c] = p[12 + c];   // node k + 1
             }
         }
     }
     __device__ __forceinline__ void drop() {
 #pragma unroll
-        for (int i = 0; i < 24; ++i) forget(v[i / 6][i % 6]);
+        for (int i = 0; i < 8 * N; ++i) forget(v[i / (2 * N)][i % (2 * N)]);
     }
     template <int c0, int c1, typename R>
     __device__ __forceinline__ void value(const FieldDev &, const CellPos<R> &at, uint32_t, R out[]) const {
         const R w[4] = {((R)1 - at.wr) * ((R)1 - at.wt), ((R)1 - at.wr) * at.wt, at.wr * ((R)1 - at.wt), at.wr * at.wt};
-        R acc[3] = {(R)0, (R)0, (R)0};
+        R acc[N] = {};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const R wa = w[q] * ((R)1 - at.wp), wb = w[q] * at.wp;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) acc[c] = fma(wb, (R)v[q][3 + c], fma(wa, (R)v[q][c], acc[c]));
+            for (int c = 0; c < N; ++c) acc[c] = fma(wb, (R)v[q][N + c], fma(wa, (R)v[q][c], acc[c]));
         }
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            if (c0 <= c && c < c1) out[c] = quad_bcast_value<0>(acc[c]);
-            if (c0 <= 3 + c && 3 + c < c1) out[3 + c] = quad_bcast_value<1>(acc[c]);
-            if (c0 <= 6 + c && 6 + c < c1) out[6 + c] = quad_bcast_value<2>(acc[c]);
-            if (c0 <= 9 + c && 9 + c < c1) out[9 + c] = quad_bcast_value<3>(acc[c]);
+        for (int c = 0; c < N; ++c) {
+            if (c0 <= c && c < c1) out[c] = group_bcast<G, 0>(acc[c]);
+            if (c0 <= N + c && N + c < c1) out[N + c] = group_bcast<G, 1>(acc[c]);
+            if constexpr (G == 4) {
+                if (c0 <= 6 + c && 6 + c < c1) out[6 + c] = group_bcast<G, 2>(acc[c]);
+                if (c0 <= 9 + c && 9 + c < c1) out[9 + c] = group_bcast<G, 3>(acc[c]);
+            }
         }
     }
 };

@@ -8,20 +8,36 @@
 namespace gc {
 
 constexpr int kMaxEnsembles = 4096;
-// Tail policy: fewer live particles than this (a share of the tail threshold T)
-// take the four-lanes-per-particle form; from there on, one lane per particle.
-// The line lies where the quad form's wavefronts begin to share a SIMD (1,024 of
-// 16 particles, T/8 of the default 131,072) or a little beyond, measured per 1,024
-// steps:
-//  * FP64 arithmetic on FP32 fields: T/8 (12,000 particles 2.26 ms in the quad form
-//    against 2.82, 20,011 3.03 against 2.90);
-//  * FP32 arithmetic, whose shorter step gains from two quad wavefronts per SIMD:
-//    T/4 (30,000 on an FP32 field 2.33 against 2.41, 50,000 the lane form);
-//  * FP64 fields, whose lane form has one wavefront per SIMD: T/4 (30,000: 2.99
-//    against 3.07 ms, 50,000: 4.65 against 3.15);
-//  * FP16 fields: never, the lane form keeps a cell in 48 registers (12,000: 3.51
-//    against 3.94 in a quad form that shared whole node pairs);
-//  * the full equations have no quad form.
+// Tail policy: lanes per particle for n live particles below the tail threshold T,
+// each line a share of T.  A form is good while its wavefronts have a SIMD each
+// (1,024 of 16, 32 or 64 particles: T/8, T/4 and T/2 of the default 131,072), and
+// fewer lanes do less work in all.  1,024 steps, in ms:
+//  * below T/8 four lanes: 12,000 particles, FP64 arithmetic on an FP32 field, 1.99
+//    against 2.27 with two; FP32 arithmetic on an FP64 field a little further, 17,000
+//    2.14 against 2.23, 20,011 2.34 against 2.23;
+//  * up to T/4 two lanes: 20,011, FP64 arithmetic, FP32 field 2.29 against 2.79 with
+//    one, FP64 field 2.25 against 2.78 with four; FP32 arithmetic, FP32 field 1.93
+//    against 2.12 with four;
+//  * then one lane: 45,000, FP64 on FP32 2.87 against 3.48 with two, FP64 on FP64
+//    3.05 against 3.27, FP32 on FP32 2.34 against 2.47; but on FP64 fields, whose
+//    one-lane form has a single wavefront per SIMD, FP32 arithmetic keeps two (45,000
+//    2.88 against 3.03, 128,000 5.28 against 5.64), and FP64 arithmetic takes two
+//    where they need three wavefronts per SIMD and one lane two rounds (T/2 to 3 T/4:
+//    90,001 4.69 against 5.41, 128,000 5.87 against 5.67);
+//  * FP16 fields: always one lane, which keeps a cell in 48 registers (12,000: 3.51
+//    against 3.94 with four that shared whole node pairs);
+//  * the full equations have no other form.
+__host__ __device__ constexpr int tail_lanes(uint32_t n, uint32_t T, bool f64_arithmetic, int field_dtype, bool full) {
+    if (full || field_dtype == GC_F16) return 1;
+    const bool f64_field = field_dtype == GC_F64;
+    if (n < T / 8 + (f64_field && !f64_arithmetic ? T / 64 : 0)) return 4;
+    if (n < T / 4) return 2;
+    if (!f64_field) return 1;
+    return !f64_arithmetic || (n >= T / 2 && n < T / 4 * 3) ? 2 : 1;
+}
+// The persistent push knows one and four lanes only, four below this line: T/8 for FP64
+// arithmetic on FP32 fields (20,011 particles 3.03 ms against 2.90 with one), T/4
+// else (30,000, FP32 arithmetic 2.33 against 2.41, FP64 field 2.99 against 3.07).
 __host__ __device__ constexpr uint32_t quad_limit(uint32_t T, bool f64_arithmetic, int field_dtype, bool full) {
     if (full || field_dtype == GC_F16) return 0;
     return f64_arithmetic && field_dtype == GC_F32 ? T / 8 : T / 4;

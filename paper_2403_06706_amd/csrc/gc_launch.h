@@ -34,7 +34,7 @@ inline void launch_timed(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStr
 }
 
 // push (gc_push.hip); form: 0 one lane per particle, 1 the same in the tail,
-// 2 four lanes per particle (for few active particles)
+// 2 four lanes per particle (for few active particles), 3 two
 hipError_t launch_push(const PushArgs &a, int precision, int block, bool persistent, int form, int grid_blocks,
                        hipStream_t s, LaunchEvents ev = {});
 

@@ -17,11 +17,16 @@ namespace gc {
 //   kFormLane   one lane per particle; a cell's nodes stay in its registers, so the loads of
 //               a gather are made on a change of cell only, all in flight at once;
 //   kFormTail   the same, below the tail threshold (the steps are counted apart);
+//   kFormPair   two lanes per particle, six components each, else as the next; counted
+//               as kFormTail;
 //   kFormQuad   four lanes per particle (an aligned quad), FP32 and FP64 fields: each lane
 //               keeps and interpolates three of the twelve components, the quad shares the
 //               results, all four run the rest of the step on identical values, lane gl = 0
 //               writes.
-enum { kFormLane = 0, kFormTail = 1, kFormQuad = 2 };
+enum { kFormLane = 0, kFormTail = 1, kFormQuad = 2, kFormPair = 3 };
+template <int FORM> constexpr uint32_t kGroup = FORM == kFormQuad ? 4 : FORM == kFormPair ? 2 : 1;   // lanes per particle
+template <int FDT, int G> struct FormCell { using type = GroupCell<FDT, G>; };
+template <int FDT> struct FormCell<FDT, 1> { using type = LaneCell<FDT>; };
 template <int FDT, int MODE> constexpr bool kHasQuad = MODE != 2 && FDT != GC_F16;
 
 // MODE 0: the reduced equations, no rebirth, centres at rest.  MODE 1: also
@@ -92,8 +97,8 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
     // a bootstrap, whose ratio is 1).
     R tau = (R)dtp0 == h ? (R)1 : h * rcp_nr((R)dtp0);
     // Resident cells: 96 registers of nodes per lane for FP32 fields, 48 FP16, 192
-    // FP64, and 168, 96 and 336 with the extra array of the full equations; a quarter
-    // in the quad form (24 or 48).
+    // FP64, and 168, 96 and 336 with the extra array of the full equations; a half in
+    // the pair form and a quarter in the quad form.
     // Bound when every gather loaded its stencil: vector issue 0.70 and the gather
     // paths (TA/TD) 0.68/0.73 busy, both evaluations of a step loading 24 x 16 bytes a
     // lane (FP64 fields 48).  An electron crosses a cell in about ten steps, so now some
@@ -101,7 +106,7 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
     // on an FP32 256x128x256 field): 2^20 electrons 2.40 -> 1.91 ms, 1,000 reborn
     // electrons in the quad form 2.09 -> 1.71 us a step; 300,007 in FP32 arithmetic 0.61
     // -> 0.39 ms; full equations, 150,000: 0.88 -> 0.72 ms.
-    using Cell = typename std::conditional<FORM == kFormQuad, QuadCell<FDT>, LaneCell<FDT>>::type;
+    using Cell = typename FormCell<FDT, kGroup<FORM>>::type;
     CellPos<R> at;
     Cell cell;
     [[maybe_unused]] typename std::conditional<FULL, LaneCell<FDT, 9>, NoCell>::type xcell;
@@ -313,7 +318,7 @@ __device__ __forceinline__ uint32_t advance_slot(const PushArgs &a, uint32_t slo
 // an equal share however small the active prefix is.
 template <int PREC, int FDT, int MODE, int FORM, bool TAME = false>
 __device__ __forceinline__ void push_grid(const PushArgs &a) {
-    constexpr uint32_t G = FORM == kFormQuad ? 4 : 1;          // lanes per particle
+    constexpr uint32_t G = kGroup<FORM>;
     const uint32_t n = *a.n_active;
     const uint32_t per_block = blockDim.x / G;                // particles per workgroup
     const uint32_t nb = (n + per_block - 1) / per_block, b = blockIdx.x;
@@ -335,13 +340,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kLaneWaves<
     push_grid<PREC, FDT, MODE, kFormLane, TAME>(a);
 }
 
-// For fewer active particles than fill the machine (quad_limit): a wavefront's
+// For fewer active particles than fill the machine (tail_lanes): a wavefront's
 // step time is then its chain of instructions and memory round trips; the quad
 // form spreads the particles over four times as many wavefronts (and compute
 // units) and interpolates a quarter of the values per lane.
 template <int PREC, int FDT, int MODE, bool TAME>
 __global__ __launch_bounds__(256) void k_push_quad(PushArgs a) {
     push_grid<PREC, FDT, MODE, kFormQuad, TAME>(a);
+}
+
+// The same for a few more particles, two lanes each.  512 steps of 20,011 electrons
+// in FP64 on the 256x128x256 FP32 field 1.46 -> 1.21 ms: two thirds of the values
+// converted, and half of the products, per lane of what was one wavefront.
+template <int PREC, int FDT, int MODE, bool TAME>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_push_pair(PushArgs a) {
+    push_grid<PREC, FDT, MODE, kFormPair, TAME>(a);
 }
 
 // Persistent forms: a fixed grid pulls tiles of consecutive slots from an
@@ -364,7 +377,7 @@ __device__ __forceinline__ void push_persistent(const PushArgs &a) {
     const uint32_t T = a.tail;
     const uint32_t quad = quad_limit(T, PREC == GC_PREC_F64, FDT, MODE == 2);
     if (FORM == kFormQuad ? n >= quad : n < quad) return;
-    constexpr uint32_t G = FORM == kFormQuad ? 4 : 1;          // lanes per particle
+    constexpr uint32_t G = kGroup<FORM>;
     const uint32_t per = blockDim.x / G;                       // particles per workgroup round
     const uint32_t share = ((n + gridDim.x - 1) / gridDim.x + per - 1) / per * per;
     const uint32_t tile = min(max((uint32_t)a.tile, per), max(per, share));
@@ -414,7 +427,12 @@ static hipError_t launch_rt(const PushArgs &a, int block, bool persistent, int f
         if (ev.stop) (void)hipEventRecord(ev.stop, s);
         return hipGetLastError();
     }
-    if constexpr (kQuad)
+    if constexpr (kQuad) {
+        if (form == kFormPair) {
+            const uint32_t pb = (2 * a.n_slots + 255) / 256;
+            launch_timed((k_push_pair<PREC, FDT, MODE, TAME>), dim3(pb), dim3(256), s, ev.start, ev.stop, a);
+            return hipGetLastError();
+        }
         if (form == kFormQuad) {
             // 256-thread workgroups whatever the block size (64 particles each;
             // measured faster for this form than 64 threads)
@@ -422,6 +440,7 @@ static hipError_t launch_rt(const PushArgs &a, int block, bool persistent, int f
             launch_timed((k_push_quad<PREC, FDT, MODE, TAME>), dim3(qb), dim3(256), s, ev.start, ev.stop, a);
             return hipGetLastError();
         }
+    }
     launch_timed((k_push<PREC, FDT, MODE, TAME>), dim3(nb), dim3(block), s, ev.start, ev.stop, a);
     return hipGetLastError();
 }
