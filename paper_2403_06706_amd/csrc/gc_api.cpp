@@ -37,7 +37,7 @@ struct MlpState {
     MlpArgs args{};
     void *mem = nullptr;
     float *p = nullptr, *mo = nullptr, *ve = nullptr, *g = nullptr;
-    __bf16 *W = nullptr, *WT = nullptr, *Wo = nullptr;   // natural order (training)
+    __bf16 *W = nullptr, *WT = nullptr, *Wo = nullptr;   // operand order (training)
     __bf16 *We = nullptr, *Woe = nullptr;                 // evaluation order (mlp_perm)
     void *ws = nullptr;
     int64_t ws_pairs = 0;

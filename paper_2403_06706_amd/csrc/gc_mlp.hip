@@ -23,10 +23,10 @@ namespace gc {
 // them back (50 MB at 16,384 rows).  A step of that size is 10 GFLOP, 8 us at the
 // rate of a large BF16 product; as one kernel per layer and pass (43 launches,
 // every activation, pre-activation and gradient through memory) it took 0.78 ms,
-// of which 0.66 ms in kernels; now 24 + 48 + 35 + 5 us.
+// of which 0.66 ms in kernels; now 15 + 34 + 17 + 5 us.
 //
 // Activations H_0..H_5 and gradients dZ_1..dZ_6 go to memory once, in BF16,
-// transposed in tiles [block][layer][128 columns][64 rows]: k_mlp_wgrad sums over
+// transposed in tiles [block][layer][64 rows / 8][128 columns][8]: k_mlp_wgrad sums over
 // rows and reads its operands, eight rows of a column, straight from there.  Rows
 // past the last repeat it with a zero gradient.  Every FP32 sum over rows is taken
 // in one order (blocks of 64 rows: even rows, odd rows; four interleaved chains
@@ -36,6 +36,14 @@ namespace gc {
 constexpr int kTrainThreads = 512;
 constexpr int kTrainPitch = kMlpWidth + 8;      // LDS row of a 64 x 128 BF16 matrix: 272 bytes, four banks a row
 constexpr size_t kTileT = (size_t)kMlpWidth * kTrainRows;   // elements of a transposed tile
+// Operand order of a matrix of n rows in memory: eight elements k of a row are 16
+// bytes, and rows follow each other, so that a wavefront's operand loads (32 rows,
+// 16 elements of each) are two runs of 512 bytes, and so are the stores of the
+// transposed tiles (whose rows are columns here).  Row after row, every load touched
+// 32 lines and used 32 bytes of each: at 16,384 rows k_mlp_wgrad 35 -> 17 us,
+// k_mlp_train 24 -> 15 and 48 -> 34.
+__host__ __device__ constexpr int operand_at(int n, int row, int k) { return ((k >> 3) * n + row) * 8 + (k & 7); }
+__device__ __forceinline__ int tile_at(int r, int c) { return operand_at(kMlpWidth, c, r); }
 
 // A wavefront owns one 32 x 32 tile of every 64 x 128 matrix (row half w / 4,
 // columns 32 (w % 4)..): its slice of the weights comes from L2 straight into
@@ -56,9 +64,13 @@ void k_mlp_train(MlpArgs m, TrainNet net, const double *pts, const double *tgt, 
     const int tid = threadIdx.x, l = tid & 63, w = tid >> 6, blk = blockIdx.x;
     const int half = l >> 5, lane = l & 31, rt = w >> 2, col = 32 * (w & 3) + lane;
     const int rows = 2 * npair, row0 = blk * kTrainRows;
-    // operand fragment s of a matrix with rows of 128 (row r, elements 16 s + 8 half ..)
+    // operand fragment s of a matrix (row r, elements 16 s + 8 half ..): in LDS by rows
+    // of `pitch`, in memory in operand order, n rows
     auto frag = [&](const __bf16 *base, size_t pitch, int r, int s) {
         return *reinterpret_cast<const bf16x8 *>(base + (size_t)r * pitch + 16 * s + 8 * half);
+    };
+    auto wfrag = [&](const __bf16 *base, int n, int r, int s) {
+        return *reinterpret_cast<const bf16x8 *>(base + operand_at(n, r, 16 * s + 8 * half));
     };
     // row of accumulator element j within the block
     auto row_of = [&](int j) { return 32 * rt + (j / 4) * 8 + half * 4 + (j % 4); };
@@ -73,12 +85,12 @@ void k_mlp_train(MlpArgs m, TrainNet net, const double *pts, const double *tgt, 
             if (lds)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) lds[row_of(4 * q + e) * kTrainPitch + col] = b[e];
-            if (T) __builtin_memcpy(T + (size_t)col * kTrainRows + row_of(4 * q), b, 8);
+            if (T) __builtin_memcpy(T + tile_at(row_of(4 * q), col), b, 8);
         }
     };
     bf16x8 bw[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) bw[s] = frag(net.W, kMlpWidth, col, s);
+    for (int s = 0; s < 8; ++s) bw[s] = wfrag(net.W, kMlpWidth, col, s);
     if constexpr (kBack) {
         if (tid < kTrainRows * kMlpOut) {               // loss and dY: one (row, output) each
             const int rl = tid / kMlpOut, c = tid % kMlpOut, r = row0 + rl, i = r < npair ? r : r - npair;
@@ -120,8 +132,8 @@ void k_mlp_train(MlpArgs m, TrainNet net, const double *pts, const double *tgt, 
         }
         if constexpr (kBack) {
             __bf16 *T = tile_t(HT, 0);
-            __builtin_memcpy(T + (size_t)(2 * j) * kTrainRows + r0, sc[0], 16);
-            __builtin_memcpy(T + (size_t)(2 * j + 1) * kTrainRows + r0, sc[1], 16);
+            __builtin_memcpy(T + tile_at(r0, 2 * j), sc[0], 16);
+            __builtin_memcpy(T + tile_at(r0, 2 * j + 1), sc[1], 16);
         }
     }
     float Z[kBack ? kMlpDepth : 1][16];
@@ -139,7 +151,8 @@ void k_mlp_train(MlpArgs m, TrainNet net, const double *pts, const double *tgt, 
                            : kBack           ? net.WT + (size_t)k * kMlpWidth * kMlpWidth
                                              : net.Wo;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) bw[s] = frag(nw, kMlpWidth, k + 1 < kMlpDepth || kBack ? col : lane, s);
+        for (int s = 0; s < 8; ++s)
+            bw[s] = k + 1 < kMlpDepth || kBack ? wfrag(nw, kMlpWidth, col, s) : wfrag(nw, kMlpOutPad, lane, s);
         float h[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
@@ -232,7 +245,7 @@ void k_mlp_train(MlpArgs m, TrainNet net, const double *pts, const double *tgt, 
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(X[(k + 1) & 1], kTrainPitch, 32 * rt + lane, s), bw[s], acc, 0, 0, 0);
             if (k > 1) {
 #pragma unroll
-                for (int s = 0; s < 8; ++s) bw[s] = frag(net.WT + (size_t)(k - 1) * kMlpWidth * kMlpWidth, kMlpWidth, col, s);
+                for (int s = 0; s < 8; ++s) bw[s] = wfrag(net.WT + (size_t)(k - 1) * kMlpWidth * kMlpWidth, kMlpWidth, col, s);
             }
 #pragma unroll
             for (int j = 0; j < 16; ++j) dH[j] = acc[j];
@@ -266,7 +279,7 @@ __global__ __launch_bounds__(512) void k_mlp_wgrad(const __bf16 *HT, const __bf1
     float s[2] = {0.0f, 0.0f};                              // elements threadIdx.x and threadIdx.x + 512
     auto load = [&](const __bf16 *T, int c0, int r0) {      // column c0 + lane, rows r0 + 8 half ..
         const __bf16 *t = T + ((size_t)(r0 >> 6) * kMlpDepth + layer) * kTileT;
-        return *reinterpret_cast<const bf16x8 *>(t + (size_t)(c0 + lane) * kTrainRows + (r0 & 63) + 8 * half);
+        return *reinterpret_cast<const bf16x8 *>(t + tile_at((r0 & 63) + 8 * half, c0 + lane));
     };
     for (int j0 = 0; j0 < len; j0 += 8) {
         const int j = j0 + w;
@@ -341,8 +354,8 @@ __global__ __launch_bounds__(256) void k_mlp_update(TrainNet net, AdamArgs a, co
         if (a.apply) {
             const int n = e / kMlpWidth, k = e % kMlpWidth;
             const __bf16 v = (__bf16)p;
-            net.W[i] = v;
-            net.WT[(size_t)layer * WW + k * kMlpWidth + n] = v;
+            net.W[(size_t)layer * WW + operand_at(kMlpWidth, n, k)] = v;
+            net.WT[(size_t)layer * WW + operand_at(kMlpWidth, k, n)] = v;
             net.We[(size_t)layer * WW + n * kMlpWidth + (layer == 0 ? k : (k & ~31) + mlp_perm_slot(k & 31))] = v;
         }
         return;
@@ -375,7 +388,7 @@ __global__ __launch_bounds__(256) void k_mlp_update(TrainNet net, AdamArgs a, co
         const float p = adam_step(net, a, i, g);
         if (a.apply && o >= nc && o < nc + nw) {
             const int e = o - nc, n = e / kMlpWidth, k = e % kMlpWidth;
-            net.Wo[e] = (__bf16)p;
+            net.Wo[operand_at(kMlpOutPad, n, k)] = (__bf16)p;
             net.Woe[n * kMlpWidth + (k & ~31) + mlp_perm_slot(k & 31)] = (__bf16)p;
         }
         return;
@@ -392,7 +405,7 @@ __global__ __launch_bounds__(256) void k_mlp_update(TrainNet net, AdamArgs a, co
     if (tid == 0) *loss_host = sum[0];
 }
 
-// W, WT, Wo: natural order (training products); We, Woe: evaluation order
+// W, WT, Wo: operand order (training products); We, Woe: evaluation order
 // (columns of layers 2..6 and of the output layer permuted by mlp_perm).
 __global__ void k_mlp_refresh(const float *p, __bf16 *W, __bf16 *WT, __bf16 *Wo, __bf16 *We, __bf16 *Woe) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -400,12 +413,12 @@ __global__ void k_mlp_refresh(const float *p, __bf16 *W, __bf16 *WT, __bf16 *Wo,
         const int layer = i / (kMlpWidth * kMlpWidth), e = i % (kMlpWidth * kMlpWidth);
         const int n = e / kMlpWidth, k = e % kMlpWidth;
         const __bf16 v = (__bf16)p[kMlpOffW + i];
-        W[i] = v;
-        WT[(size_t)layer * kMlpWidth * kMlpWidth + k * kMlpWidth + n] = v;
+        W[(size_t)layer * kMlpWidth * kMlpWidth + operand_at(kMlpWidth, n, k)] = v;
+        WT[(size_t)layer * kMlpWidth * kMlpWidth + operand_at(kMlpWidth, k, n)] = v;
         const int ks = layer == 0 ? k : (k & ~31) + mlp_perm(k & 31);
         We[i] = (__bf16)p[kMlpOffW + (size_t)layer * kMlpWidth * kMlpWidth + n * kMlpWidth + ks];
     }
-    if (i < kMlpOutPad * kMlpWidth) Wo[i] = (__bf16)p[kMlpOffWo + i];
+    if (i < kMlpOutPad * kMlpWidth) Wo[operand_at(kMlpOutPad, i / kMlpWidth, i % kMlpWidth)] = (__bf16)p[kMlpOffWo + i];
     if (i < kMlpEvalRows * kMlpWidth) {
         const int n = i / kMlpWidth, k = i % kMlpWidth;
         Woe[i] = n < kMlpOut ? (__bf16)p[kMlpOffWo + n * kMlpWidth + (k & ~31) + mlp_perm(k & 31)] : (__bf16)0.0f;
