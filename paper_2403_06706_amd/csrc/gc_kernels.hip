@@ -126,9 +126,13 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s) {
 
 // Slots to injection order.  Scattered stores of 25 arrays wrote whole lines for 4
 // or 8 bytes each (2^20 particles: 0.42 ms for 172 bytes read and written a
-// particle), so the order is inverted first and the arrays are gathered, one after
-// the other (blockIdx.y) so that the array being read stays in the caches, four
-// particles a thread.
+// particle), so the order is inverted first and the arrays are gathered, four
+// particles a thread.  Each XCD (workgroups go to them round-robin) takes two of the
+// first sixteen FP64 arrays, one after the other, and one of the 32-bit arrays: read by
+// one XCD, an array comes into one L2 (4 MB: 500,000 particles) once.  Gathered by all
+// of them it came into eight: 300,007 particles 56 -> 34 us, 500,000 104 -> 75; the last
+// two FP64 arrays still are.  Past kOutFits an array overflows the one L2 by so much
+// that every XCD gathers from every array (2^20 particles: 160 us against 166).
 __global__ void k_invert(const uint32_t *gid, uint32_t *inv, uint32_t n) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) inv[gid[i]] = i;
@@ -141,8 +145,10 @@ struct StateOut {
 constexpr int kOutDoubles = 18, kOutArrays = 25;
 
 template <typename T>
-__device__ __forceinline__ void gather4(const T *src, T *dst, const uint32_t *inv, uint32_t n) {
-    const uint32_t g0 = blockIdx.x * blockDim.x * 4 + threadIdx.x;
+__device__ __forceinline__ void gather4(const void *from, void *to, const uint32_t *inv, uint32_t chunk, uint32_t n) {
+    const T *src = static_cast<const T *>(from);
+    T *dst = static_cast<T *>(to);
+    const uint32_t g0 = chunk * blockDim.x * 4 + threadIdx.x;
     uint32_t at[4];
     T v[4];
 #pragma unroll
@@ -154,11 +160,28 @@ __device__ __forceinline__ void gather4(const T *src, T *dst, const uint32_t *in
         if (g0 + q * blockDim.x < n) dst[g0 + q * blockDim.x] = v[q];
 }
 
-__global__ __launch_bounds__(256) void k_state_out(StateOut a, const uint32_t *inv, uint32_t n) {
-    const int y = blockIdx.y;
-    if (!a.dst[y]) return;
-    if (y < kOutDoubles) gather4(static_cast<const uint64_t *>(a.src[y]), static_cast<uint64_t *>(a.dst[y]), inv, n);
-    else gather4(static_cast<const uint32_t *>(a.src[y]), static_cast<uint32_t *>(a.dst[y]), inv, n);
+constexpr uint32_t kOutXcds = 8, kOutShared = 16;           // FP64 arrays [0, kOutShared): two per XCD
+static_assert(2 * kOutXcds == kOutShared && kOutDoubles >= (int)kOutShared &&
+              kOutArrays - kOutDoubles <= (int)kOutXcds, "array shares");
+
+constexpr uint32_t kOutFits = 786432;                       // particles: 6 MB an FP64 array
+
+// nb workgroups per array; the arrays from `shared` on (kOutShared, or 0: all) by all XCDs
+__global__ __launch_bounds__(256) void k_state_out(StateOut a, const uint32_t *inv, uint32_t nb, uint32_t shared,
+                                                   uint32_t n) {
+    const uint32_t b = blockIdx.x, own = shared ? 3 * kOutXcds * nb : 0;
+    uint32_t y, chunk;
+    if (b < own) {
+        const uint32_t xcd = b % kOutXcds, pos = b / kOutXcds, item = pos / nb;
+        chunk = pos % nb;
+        y = item < 2 ? 2 * xcd + item : kOutDoubles + xcd;
+    } else {
+        y = shared + (b - own) / nb;
+        chunk = (b - own) % nb;
+    }
+    if (y >= (uint32_t)kOutArrays || !a.dst[y]) return;
+    if (y < (uint32_t)kOutDoubles) gather4<uint64_t>(a.src[y], a.dst[y], inv, chunk, n);
+    else gather4<uint32_t>(a.src[y], a.dst[y], inv, chunk, n);
 }
 
 __global__ void k_state_in(SoA st, gc_state_view src, uint32_t n) {
@@ -180,7 +203,10 @@ hipError_t launch_state_out(const SoA &st, const gc_state_view &dst, uint32_t n,
     GC_FOR_U32(OUT_)
 #undef OUT_
     hipLaunchKernelGGL(k_invert, dim3((n + 255) / 256), dim3(256), 0, s, st.gid, inv, n);
-    hipLaunchKernelGGL(k_state_out, dim3((n + 1023) / 1024, kOutArrays), dim3(256), 0, s, a, inv, n);
+    const uint32_t nb = (n + 1023) / 1024;
+    const uint32_t shared = n <= kOutFits ? kOutShared : 0;
+    const uint32_t arrays = shared ? 3 * kOutXcds + kOutDoubles - kOutShared : kOutArrays;
+    hipLaunchKernelGGL(k_state_out, dim3(nb * arrays), dim3(256), 0, s, a, inv, nb, shared, n);
     return hipGetLastError();
 }
 hipError_t launch_state_in(const SoA &st, const gc_state_view &src, uint32_t n, hipStream_t s) {
